@@ -171,11 +171,9 @@ __device__ __forceinline__ void block_range(int64_t Nn, int64_t &n0, int64_t &n1
 __device__ __forceinline__ bool stopped(const KrylovScalars *sc) { return sc->converged | sc->breakdown; }
 
 // Persistent SpMV over this block's contiguous node range.  The range's row
-// pointers are staged in LDS once; each 32-lane group then takes P nodes at a time
-// and issues all their column-index and value loads before any of them is used, so
-// a wave keeps P times more HBM traffic in flight than a one-node-at-a-time walk,
-// and the next P nodes' loads are issued before the current x gathers are awaited.
-// Lane l of a group handles neighbour block l of each of its nodes (node degrees
+// pointers are staged in LDS once; each 32-lane group then takes one node at a time,
+// and the next node's index and value loads are issued before the current x gathers
+// are awaited.  Lane l of a group handles neighbour block l of its node (node degrees
 // above 32 fall back to a strided loop); the ND row sums are finished with a
 // reduce-scatter over the group (a row swap and four DPP steps, no LDS traffic).
 // Row results are kept in LDS and written (with the dot-product terms) after the
@@ -185,29 +183,34 @@ __device__ __forceinline__ bool stopped(const KrylovScalars *sc) { return sc->co
 // MODE 0: y = alpha K x + beta y
 // MODE 1: y = K x and alpha = rho / (w0, y)                 (BiCGSTAB v = K ph, CG q = K p)
 // MODE 2: y = K x and omega = (w0, y) / (y, y), w0 = s      (BiCGSTAB t = K sh)
+//
+// What bounds it: bytes from HBM, or from the 256 MB Infinity Cache when the matrix
+// fits there.  The values are read with ordinary (cached) loads: a lane's 12- or 24-byte
+// pieces and the rows of neighbouring nodes share cache lines, which non-temporal loads
+// gave up before their second use, and they also kept small matrices out of the
+// Infinity Cache.  One node in flight per group and few resident blocks (spmv_grid):
+// the fewer streams an XCD runs, the more of the x gathers and split lines its 4 MB L2
+// serves.  Back-to-back products on box meshes, non-temporal loads with 4 / 4 / 2 nodes
+// in flight on every resident block against this form:
+//   FP64, 100^3 (2.08 GB)     461.8 -> 352.2 us (4.50 -> 5.89 TB/s)
+//   FP64, 64x32x32 (138 MB)    36.8 ->  22.4 us (3.76 -> 6.17 TB/s)
+//   FP64, 24x24x48 (59 MB)     17.7 ->  11.2 us
+//   FP32, 100^3 (1.07 GB)     202.9 -> 183.6 us (5.27 -> 5.82 TB/s)
+//   FP32, 64^3 (282 MB)        57.8 ->  44.4 us
+//   FP32 values under FP64 vectors, 100^3   221.5 -> 203.8 us; 40^3  17.3 -> 13.2 us
+//   one dof per node, FP64, 50x50x10         7.6 ->   4.8 us
+// (a plain read of the same values takes 325, 20, 7.4-8.5, 176, 41 us).
 constexpr int kSpmvGroup = 32;
 constexpr int kMaxChunk = 1024;  // nodes per block staged in LDS
 
-// Nodes in flight per 32-lane group: as many as fit with the double-buffered loads
-// at an occupancy of four (FP32 values) or two (FP64 values) wavefronts per SIMD.
-// TV is the type of the stored values.  FP32 values under FP64 vectors (the mixed form
-// with FP64 Krylov vectors): four nodes at three wavefronts per SIMD (149 registers;
-// measured 243 us per launch at the 100^3 workload against 254 us with three nodes at
-// four wavefronts, which fit in 128).
-template <int ND, typename TV, typename T = TV>
-constexpr int spmv_batch() { return ND == 1 ? 4 : (sizeof(TV) == 4 ? 4 : 2); }
-
-template <typename TV, typename T>
-constexpr int spmv_waves() { return sizeof(TV) == 4 ? (sizeof(T) == 4 ? 4 : 3) : 2; }
-
-template <int ND, int P, int MODE, typename T, bool D16, typename TV = T>
-__global__ __launch_bounds__(kThreads, (spmv_waves<TV, T>())) void k_spmv_nodes(int64_t Nn, const int64_t *__restrict__ node_ptr,
-                                                         const int32_t *__restrict__ node_nb,
-                                                         const int16_t *__restrict__ node_dnb,
-                                                         const TV *__restrict__ values, const T *__restrict__ x,
-                                                         T *__restrict__ y, const T *__restrict__ w0, T alpha,
-                                                         T beta, double *partials, KrylovScalars *sc, int cg,
-                                                         int big) {
+template <int ND, int MODE, typename T, bool D16, typename TV = T>
+__global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const int64_t *__restrict__ node_ptr,
+                                                            const int32_t *__restrict__ node_nb,
+                                                            const int16_t *__restrict__ node_dnb,
+                                                            const TV *__restrict__ values, const T *__restrict__ x,
+                                                            T *__restrict__ y, const T *__restrict__ w0, T alpha,
+                                                            T beta, double *partials, KrylovScalars *sc, int cg,
+                                                            int big) {
     constexpr int G = kSpmvGroup;
     constexpr int GPB = kThreads / G;  // groups per block
     static_assert(G == 32 && (ND == 1 || ND == 3), "32-lane groups, 1 or 3 dofs per node");
@@ -229,68 +232,52 @@ __global__ __launch_bounds__(kThreads, (spmv_waves<TV, T>())) void k_spmv_nodes(
         __syncthreads();  // previous sub-chunk finished with sptr
         for (int i = threadIdx.x; i <= cnt; i += kThreads) sptr[i] = node_ptr[n0 + i];
         __syncthreads();
-        int64_t b0[P];
-        int deg[P];
-        int32_t m[P];
-        TV v[P][ND][ND];
-        // Column indices and values of P nodes.  Addresses are clamped (a slot past the
+        int deg;
+        int32_t m;
+        TV v[ND][ND];
+        // Column index and values of one node.  Addresses are clamped (a node past the
         // chunk re-reads its last node, a lane past the degree reads block 0), so the
         // loads are branch-free; the results of such slots are masked.
-        auto load_batch = [&](int base) {
+        auto load_node = [&](int ln) {
+            ln = ln < cnt ? ln : cnt - 1;
+            const int64_t b0 = sptr[ln];
+            deg = int(sptr[ln + 1] - b0);
+            const int lc = lane < deg ? lane : 0;
+            if constexpr (D16) m = int32_t(n0 + ln) + int32_t(node_dnb[b0 + lc]);
+            else m = node_nb[b0 + lc];
+            const TV *vb = values + int64_t(ND) * ND * b0 + ND * lc;
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                int ln = base + p * GPB;
-                ln = ln < cnt ? ln : cnt - 1;
-                b0[p] = sptr[ln];
-                deg[p] = int(sptr[ln + 1] - b0[p]);
-                const int lc = lane < deg[p] ? lane : 0;
-                if constexpr (D16)
-                    m[p] = int32_t(n0 + ln) + int32_t(__builtin_nontemporal_load(node_dnb + b0[p] + lc));
-                else
-                    m[p] = __builtin_nontemporal_load(node_nb + b0[p] + lc);
-                const TV *vb = values + int64_t(ND) * ND * b0[p] + ND * lc;
+            for (int i = 0; i < ND; ++i)
 #pragma unroll
-                for (int i = 0; i < ND; ++i)
-#pragma unroll
-                    for (int k = 0; k < ND; ++k)
-                        v[p][i][k] = __builtin_nontemporal_load(vb + int64_t(i) * ND * deg[p] + k);
-            }
+                for (int k = 0; k < ND; ++k) v[i][k] = vb[int64_t(i) * ND * deg + k];
         };
-        load_batch(grp);
-        for (int base = grp; base < cnt; base += P * GPB) {
-            // Software pipeline: the x gathers of this batch go out first, then the next
-            // batch's index and value loads, so waiting for the gathers leaves the next
-            // batch in flight (memory counters complete in issue order).
-            T xm[P][ND];
-            TV cv[P][ND][ND];
-            int cdeg[P];
+        load_node(grp);
+        for (int ln = grp; ln < cnt; ln += GPB) {
+            // Software pipeline: the x gathers of this node go out first, then the next
+            // node's index and value loads, so waiting for the gathers leaves the next
+            // node in flight (memory counters complete in issue order).
+            T xm[ND];
+            TV cv[ND][ND];
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
+            for (int k = 0; k < ND; ++k) xm[k] = x[int64_t(ND) * m + k];
+            const int cdeg = deg;
 #pragma unroll
-                for (int k = 0; k < ND; ++k) xm[p][k] = x[int64_t(ND) * m[p] + k];
-                cdeg[p] = deg[p];
+            for (int i = 0; i < ND; ++i)
 #pragma unroll
-                for (int i = 0; i < ND; ++i)
+                for (int k = 0; k < ND; ++k) cv[i][k] = v[i][k];
+            load_node(ln + GPB);
+            T acc[ND];
 #pragma unroll
-                    for (int k = 0; k < ND; ++k) cv[p][i][k] = v[p][i][k];
+            for (int i = 0; i < ND; ++i) {
+                T a = T(0);
+#pragma unroll
+                for (int k = 0; k < ND; ++k) a += T(cv[i][k]) * xm[k];
+                acc[i] = lane < cdeg ? a : T(0);
             }
-            load_batch(base + P * GPB);
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                T acc[ND];
-#pragma unroll
-                for (int i = 0; i < ND; ++i) {
-                    T a = T(0);
-#pragma unroll
-                    for (int k = 0; k < ND; ++k) a += T(cv[p][i][k]) * xm[p][k];
-                    acc[i] = lane < cdeg[p] ? a : T(0);
-                }
-                T sv;
-                if constexpr (ND == 3) sv = group32_sum3(acc[0], acc[1], acc[2], lane);
-                else sv = group32_sum(acc[0], lane);
-                const int ln = base + p * GPB;
-                if (ln < cnt && row >= 0) sy[ND * ln + row] = sv;
-            }
+            T sv;
+            if constexpr (ND == 3) sv = group32_sum3(acc[0], acc[1], acc[2], lane);
+            else sv = group32_sum(acc[0], lane);
+            if (row >= 0) sy[ND * ln + row] = sv;
         }
         __syncthreads();
         if (big) {  // neighbours beyond the 32nd of high-degree nodes (none on structured meshes)
@@ -1180,6 +1167,16 @@ static int resident_grid(const fem_handle *h, K kernel) {
     return std::max(8, (G / 8) * 8);
 }
 
+// Grid of k_spmv_nodes, by the size of the stored values: two blocks per CU for 8-byte
+// values (100^3: 352 us; three or four 385 us, one node more in flight 374 us), three
+// for 4-byte values (100^3: 183.6 us; two 217.5 us, seven 207.7 us).  Products with one
+// dof per node are too short to be bound by bytes (50x50x10: 4.8 us with eight, 6.3 us
+// with two).
+template <int ND, typename TV>
+static int spmv_grid(const fem_handle *h) {
+    return (ND == 1 ? 8 : (sizeof(TV) == 8 ? 2 : 3)) * h->num_cus;
+}
+
 size_t krylov_partials_bytes(const fem_handle *h) { return size_t(krylov_grid(h)) * 3 * sizeof(double); }
 
 template <int ND, int G, typename T>
@@ -1191,13 +1188,13 @@ static void spmv_launch(const fem_handle *h, const T *values, int transpose, con
         hipLaunchKernelGGL((k_spmv<ND, G, true, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr, g.node_nb, g.mirror,
                            values, x, y, alpha, beta);
     else if (g.node_dnb)
-        hipLaunchKernelGGL((k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, true>),
-                           dim3(resident_grid(h, k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, true>)),
+        hipLaunchKernelGGL((k_spmv_nodes<ND, 0, T, true>),
+                           dim3(spmv_grid<ND, T>(h)),
                            dim3(kThreads), 0, s, g.Nn, g.node_ptr, g.node_nb, g.node_dnb, values, x, y, nullptr,
                            alpha, beta, nullptr, nullptr, 0, int(g.max_deg > kSpmvGroup));
     else
-        hipLaunchKernelGGL((k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, false>),
-                           dim3(resident_grid(h, k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, false>)),
+        hipLaunchKernelGGL((k_spmv_nodes<ND, 0, T, false>),
+                           dim3(spmv_grid<ND, T>(h)),
                            dim3(kThreads), 0, s, g.Nn, g.node_ptr, g.node_nb, g.node_dnb, values, x, y, nullptr,
                            alpha, beta, nullptr, nullptr, 0, int(g.max_deg > kSpmvGroup));
 }
@@ -1287,27 +1284,27 @@ void kry_cg_init(const fem_handle *h, const KrylovVecs<T> &k, const T *b, double
 
 // Launches the fused SpMV (partials into k.partials) and, unless the caller folds it
 // into its next kernel, the one-block finalize; returns the SpMV grid size.
-template <int ND, int P, int MODE, typename T, typename TV = T>
+template <int ND, int MODE, typename T, typename TV = T>
 static int kry_spmv_launch(const fem_handle *h, const T *x, T *y, const T *w0, const KrylovVecs<T> &k, int cg,
                            const TV *values, bool finalize, hipStream_t s) {
     const Graph &g = h->g;
     int G;
     if (k.layout == LAYOUT_SYM) {
         if constexpr (std::is_same<T, TV>::value) {
-            G = resident_grid(h, k_spmv_sym<ND, P, MODE, T>);
-            hipLaunchKernelGGL((k_spmv_sym<ND, P, MODE, T>), dim3(G), dim3(kThreads), 0, s, g.Nn, g.node_ptr,
+            G = resident_grid(h, k_spmv_sym<ND, 4, MODE, T>);
+            hipLaunchKernelGGL((k_spmv_sym<ND, 4, MODE, T>), dim3(G), dim3(kThreads), 0, s, g.Nn, g.node_ptr,
                                g.up_base, g.node_nb, g.lo_val, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg);
         } else {
             throw Error(FEM_EINVAL, "the symmetric block layout takes values of the vector type");
         }
     } else if (g.node_dnb) {
-        G = resident_grid(h, k_spmv_nodes<ND, P, MODE, T, true, TV>);
-        hipLaunchKernelGGL((k_spmv_nodes<ND, P, MODE, T, true, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
+        G = spmv_grid<ND, TV>(h);
+        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, true, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
                            g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg,
                            int(g.max_deg > kSpmvGroup));
     } else {
-        G = resident_grid(h, k_spmv_nodes<ND, P, MODE, T, false, TV>);
-        hipLaunchKernelGGL((k_spmv_nodes<ND, P, MODE, T, false, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
+        G = spmv_grid<ND, TV>(h);
+        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, false, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
                            g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg,
                            int(g.max_deg > kSpmvGroup));
     }
@@ -1326,14 +1323,14 @@ static int kry_spmv(const fem_handle *h, const T *x, T *y, const T *w0, const Kr
     if constexpr (sizeof(T) == 8) {
         if (k.A32) {
             if (h->g.nd == 1)
-                return kry_spmv_launch<1, spmv_batch<1, float, T>(), MODE, T, float>(h, x, y, w0, k, cg, k.A32,
+                return kry_spmv_launch<1, MODE, T, float>(h, x, y, w0, k, cg, k.A32,
                                                                                      finalize, s);
-            return kry_spmv_launch<3, spmv_batch<3, float, T>(), MODE, T, float>(h, x, y, w0, k, cg, k.A32, finalize,
+            return kry_spmv_launch<3, MODE, T, float>(h, x, y, w0, k, cg, k.A32, finalize,
                                                                                  s);
         }
     }
-    if (h->g.nd == 1) return kry_spmv_launch<1, spmv_batch<1, T>(), MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
-    return kry_spmv_launch<3, spmv_batch<3, T>(), MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
+    if (h->g.nd == 1) return kry_spmv_launch<1, MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
+    return kry_spmv_launch<3, MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
 }
 
 template <typename T>
@@ -1359,8 +1356,8 @@ void launch_spmv_sc(const fem_handle *h, const T *values, const T *x, T *y, T al
     if (g.N == 0) return;
     KrylovScalars *scw = const_cast<KrylovScalars *>(sc);
 #define FEM_SPMV_SC(ND, D16)                                                                                       \
-    hipLaunchKernelGGL((k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, D16>),                                         \
-                       dim3(resident_grid(h, k_spmv_nodes<ND, spmv_batch<ND, T>(), 0, T, D16>)), dim3(kThreads), 0, \
+    hipLaunchKernelGGL((k_spmv_nodes<ND, 0, T, D16>),                                         \
+                       dim3(spmv_grid<ND, T>(h)), dim3(kThreads), 0, \
                        s, g.Nn, g.node_ptr, g.node_nb, g.node_dnb, values, x, y, nullptr, alpha, beta, nullptr,   \
                        scw, 0, int(g.max_deg > kSpmvGroup))
     if (g.nd == 1) {
