@@ -49,23 +49,6 @@ __device__ __forceinline__ bool halted(const KrylovScalars *sc) {
     return sc != nullptr && (sc->converged | sc->breakdown);
 }
 
-// Sum over the 64 lanes of a wavefront; every lane receives it (fixed order).
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-    v = lane_sum16(v);
-    v += swap_rows(v, v, (threadIdx.x & 31) >= 16);
-    v += __shfl_xor(v, 32, 64);
-    return v;
-}
-
-// Sum over the 32-lane half of a wavefront holding this lane; every lane receives it.
-template <typename T>
-__device__ __forceinline__ T half_sum(T v) {
-    v = lane_sum16(v);
-    v += swap_rows(v, v, (threadIdx.x & 31) >= 16);
-    return v;
-}
-
 // ------------------------------------------------------------------ coarse operator
 // One 32-lane group per coarse block c = (I, J): sum over its fine blocks (i, j) of
 // P_i^T A_ij P_j.

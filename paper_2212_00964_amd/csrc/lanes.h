@@ -70,6 +70,23 @@ __device__ __forceinline__ double swap_rows(double a, double b, bool upper) {
     return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
+// Sum over the 32-lane half of a wavefront holding this lane (all 32 lanes receive it).
+template <typename T>
+__device__ __forceinline__ T half_sum(T v) {
+    v = lane_sum16(v);
+    v += swap_rows(v, v, (threadIdx.x & 31) >= 16);
+    return v;
+}
+
+// Sum over the 64 lanes of a wavefront (all lanes receive it, in one fixed order): five
+// register moves and one trip through the LDS crossbar.
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+    v = half_sum(v);
+    v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
 // Sum over a 32-lane group; lane 0 of the group holds the total.
 template <typename T>
 __device__ __forceinline__ T group32_sum(T a, int lane32) {
