@@ -253,6 +253,9 @@ template <typename T>
 void kry_bicg_check(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_t s);
 template <typename T>
 void kry_cg_init(const fem_handle *h, const KrylovVecs<T> &k, const T *b, double rtol, hipStream_t s);
+// Likewise for CG when its SpMV forms the next direction (nothing to do otherwise).
+template <typename T>
+void kry_cg_check(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_t s);
 // Two-level preconditioned CG (amg.hip): init (z = M b) and iteration `it`.
 template <typename T>
 void kry_cg_amg_init(fem_handle *h, const KrylovVecs<T> &k, const T *b, double rtol, hipStream_t s);

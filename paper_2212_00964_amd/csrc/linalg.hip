@@ -162,6 +162,144 @@ __device__ __forceinline__ void block_range(int64_t Nn, int64_t &n0, int64_t &n1
 
 __device__ __forceinline__ bool stopped(const KrylovScalars *sc) { return sc->converged | sc->breakdown; }
 
+// ------------------------------------------------------------------ Krylov scalars
+// The scalar updates of the fused CG and BiCGSTAB iterations.  Every block of the kernel
+// that needs them sums the previous kernel's partials itself, in the same order, so all
+// blocks agree bit for bit; block 0 publishes the scalars.  They return false when the
+// iteration stops here (converged or broken down).
+
+// CG after iteration it: rho = (r, z), |r|^2; convergence test; beta = rho / rho_pp[it & 1].
+__device__ bool cg_p_scalars(const double *partials, int count, KrylovScalars *sc, int it, double &beta) {
+    double tot[2];
+    sum_partials<2>(partials, count, tot);
+    const double rho_prev = sc->rho_pp[it & 1];
+    const bool nan = !isfinite(tot[0]) || !isfinite(tot[1]);
+    const bool conv = !nan && tot[1] <= sc->tol2;
+    beta = tot[0] / rho_prev;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->rho_old = rho_prev;
+        sc->rho = tot[0];
+        sc->rho_pp[(it + 1) & 1] = tot[0];
+        sc->beta = beta;
+        sc->rnorm2 = tot[1];
+        sc->its = it + 1;
+        if (nan) sc->breakdown = 2;
+        else if (conv) sc->converged = 1;
+    }
+    return !(nan || conv);
+}
+
+// Finite-precision safeguards of the fused BiCGSTAB, for FP32 vectors.  Omega limit:
+// when t and s are nearly orthogonal (|(t, s)| < Omega |t| |s|), omega = (t, s) / (t, t)
+// is scaled up by Omega / cos(t, s), which keeps the BiCG coefficients of the next
+// steps accurate (Sleijpen and van der Vorst's 'limited omega', Omega = 0.7).  Restart
+// floor: see bicg_rho_floor.  Measured on the 5-step 100^3 and 200x100x100 neo-Hookean
+// solves: FP32 sweeps without the floor diverged on the larger one; the limit cut its
+// FP32 iterations by a third (27,704 against 41,951) but cost the FP64 vectors 48% more
+// (23,236 against 15,705), so FP64 runs plain BiCGSTAB.
+constexpr double kOmegaLimitF32 = 0.7;
+constexpr double kRhoFloorF32 = 1e-5;
+
+template <typename T>
+__device__ __forceinline__ double bicg_omega_limit() { return sizeof(T) == 4 ? kOmegaLimitF32 : 0.0; }
+
+struct BicgStart {
+    double rho, r2, rh2, rmin2;
+    bool nan, conv, div, restart;
+};
+
+// Restart floor of |(rhat, r)| / (|rhat| |r|): below it the shadow inner product has
+// lost its meaning.  In FP32 the vectors carry relative errors near 1e-7 that grow over
+// long solves, so the floor sits well above that noise; FP64 keeps the classic 1e-9.
+template <typename T>
+__device__ __forceinline__ double bicg_rho_floor() { return sizeof(T) == 4 ? kRhoFloorF32 : 1e-9; }
+
+// Tests at the start of iteration i (>= 1) from the partial sums tot = ((rhat, r), |r|^2)
+// of iteration i - 1: the same rules as the unfused finalize.
+__device__ BicgStart bicg_start(const double tot[2], const KrylovScalars *sc, int i, double rho_floor) {
+    const int q = (i - 1) & 1;
+    BicgStart b;
+    b.r2 = tot[1];
+    b.nan = !isfinite(tot[0]) || !isfinite(tot[1]);
+    b.conv = !b.nan && tot[1] <= sc->tol2;
+    b.div = !b.nan && !b.conv && tot[1] > 1e12 * sc->bnorm2;
+    const double rh2 = sc->rh2_pp[q], rmin2 = sc->rmin2_pp[q];
+    // (rhat, r) lost its size relative to |rhat||r|, omega vanished, or the residual
+    // grew 1000x above its best value: restart from the current r
+    b.restart = !(fabs(tot[0]) > rho_floor * sqrt(rh2 * tot[1])) || sc->omega_pp[q] == 0.0 || tot[1] > 1e6 * rmin2;
+    b.rho = b.restart ? tot[1] : tot[0];
+    b.rh2 = b.restart ? tot[1] : rh2;
+    b.rmin2 = fmin(rmin2, tot[1]);
+    return b;
+}
+
+__device__ __forceinline__ void bicg_publish_start(const BicgStart &b, KrylovScalars *sc, int i) {
+    sc->its = i;
+    sc->rnorm2 = b.r2;
+    if (b.nan) sc->breakdown = 2;
+    else if (b.conv) sc->converged = 1;
+    else if (b.div) sc->breakdown = 1;
+}
+
+// BiCGSTAB at the start of iteration it: p = r + beta (p - omega v), or p = r on a restart.
+template <typename T>
+__device__ bool bicg_p_scalars(const double *partials, int count, KrylovScalars *sc, int it, double &beta,
+                               double &omega, bool &restart) {
+    restart = false;
+    beta = omega = 0.0;
+    if (it == 0) return true;
+    double tot[2];
+    sum_partials<2>(partials, count, tot);
+    const BicgStart b = bicg_start(tot, sc, it, bicg_rho_floor<T>());
+    const int q = (it - 1) & 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        bicg_publish_start(b, sc, it);
+        sc->rho_old = sc->rho_pp[q];
+        sc->rho = b.rho;
+        sc->rho_pp[it & 1] = b.rho;
+        sc->rh2_pp[it & 1] = b.rh2;
+        sc->rmin2_pp[it & 1] = b.rmin2;
+        if (b.restart) sc->restart_at = it;
+    }
+    if (b.nan || b.conv || b.div) return false;
+    restart = b.restart;
+    omega = sc->omega_pp[q];
+    if (!restart) beta = (b.rho / sc->rho_pp[q]) * (sc->alpha_pp[q] / omega);
+    return true;
+}
+
+// BiCGSTAB in iteration it: alpha = rho_it / (rhat, v), s = r - alpha v.
+__device__ bool bicg_s_scalars(const double *partials, int count, KrylovScalars *sc, int it, double &alpha) {
+    double tot[1];
+    sum_partials<1>(partials, count, tot);
+    if (!(tot[0] != 0.0) || !isfinite(tot[0])) {  // (rhat, v) vanished
+        if (blockIdx.x == 0 && threadIdx.x == 0) sc->breakdown = 1;
+        return false;
+    }
+    alpha = sc->rho_pp[it & 1] / tot[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->alpha_pp[it & 1] = alpha;
+        sc->alpha = alpha;
+    }
+    return true;
+}
+
+// How k_spmv_nodes gets its input vector: read it (GATHER_X), or form it from the
+// iteration's vectors while gathering, which saves the vector kernel that would write it
+// first.  The block writes its own rows of the formed vector to `out`.
+//   GATHER_CG_P:   p = z + beta p_old                      x = z, b = p_old
+//   GATHER_BICG_P: p = r + beta (p_old - omega v_old)      x = r, b = p_old, c = v_old
+//                  (on a restart p = r, and rh = r)
+//   GATHER_BICG_S: s = r - alpha v                         x = r, b = v
+enum { GATHER_X = 0, GATHER_CG_P = 1, GATHER_BICG_P = 2, GATHER_BICG_S = 3 };
+template <typename T>
+struct GatherIn {
+    const T *b = nullptr, *c = nullptr;
+    T *out = nullptr, *rh = nullptr;
+    const double *partials = nullptr;  // of the kernel before (count of them)
+    int count = 0, it = 0;
+};
+
 // Persistent SpMV over this block's contiguous node range.  The range's row
 // pointers are staged in LDS once; each 32-lane group then takes one node at a time,
 // and the next node's index and value loads are issued before the current x gathers
@@ -195,14 +333,14 @@ __device__ __forceinline__ bool stopped(const KrylovScalars *sc) { return sc->co
 constexpr int kSpmvGroup = 32;
 constexpr int kMaxChunk = 1024;  // nodes per block staged in LDS
 
-template <int ND, int MODE, typename T, bool D16, typename TV = T>
+template <int ND, int MODE, typename T, bool D16, typename TV = T, int GATHER = GATHER_X>
 __global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const int64_t *__restrict__ node_ptr,
                                                             const int32_t *__restrict__ node_nb,
                                                             const int16_t *__restrict__ node_dnb,
                                                             const TV *__restrict__ values, const T *__restrict__ x,
                                                             T *__restrict__ y, const T *__restrict__ w0, T alpha,
                                                             T beta, double *partials, KrylovScalars *sc, int cg,
-                                                            int big) {
+                                                            int big, GatherIn<T> gi = GatherIn<T>()) {
     constexpr int G = kSpmvGroup;
     constexpr int GPB = kThreads / G;  // groups per block
     static_assert(G == 32 && (ND == 1 || ND == 3), "32-lane groups, 1 or 3 dofs per node");
@@ -213,6 +351,29 @@ __global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const in
     if ((MODE != 0 || sc != nullptr) && stopped(sc)) return;  // MODE 0 with sc: inside a Krylov loop
     if (MODE != 0)
         for (int c = 0; c < NDOT; ++c) sdot[c * kThreads + threadIdx.x] = 0.0;
+    T c1 = T(0), c2 = T(0);
+    bool restart = false;
+    if constexpr (GATHER == GATHER_CG_P) {
+        double beta1 = 0.0;
+        if (gi.it > 0 && !cg_p_scalars(gi.partials, gi.count, sc, gi.it - 1, beta1)) return;
+        c1 = T(beta1);
+    } else if constexpr (GATHER == GATHER_BICG_P) {
+        double beta1, omega;
+        if (!bicg_p_scalars<T>(gi.partials, gi.count, sc, gi.it, beta1, omega, restart)) return;
+        c1 = T(beta1);
+        c2 = T(omega);
+    } else if constexpr (GATHER == GATHER_BICG_S) {
+        double alpha1;
+        if (!bicg_s_scalars(gi.partials, gi.count, sc, gi.it, alpha1)) return;
+        c1 = T(alpha1);
+    }
+    auto input = [&](int64_t d) -> T {
+        const T a = x[d];
+        if constexpr (GATHER == GATHER_CG_P) return a + c1 * gi.b[d];
+        else if constexpr (GATHER == GATHER_BICG_P) return restart ? a : a + c1 * (gi.b[d] - c2 * gi.c[d]);
+        else if constexpr (GATHER == GATHER_BICG_S) return a - c1 * gi.b[d];
+        else return a;
+    };
     int64_t r0, r1;
     block_range(Nn, r0, r1);
     const int lane = threadIdx.x % G;
@@ -251,7 +412,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const in
             T xm[ND];
             TV cv[ND][ND];
 #pragma unroll
-            for (int k = 0; k < ND; ++k) xm[k] = x[int64_t(ND) * m + k];
+            for (int k = 0; k < ND; ++k) xm[k] = input(int64_t(ND) * m + k);
             const int cdeg = deg;
 #pragma unroll
             for (int i = 0; i < ND; ++i)
@@ -286,7 +447,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const in
 #pragma unroll
                     for (int i = 0; i < ND; ++i)
 #pragma unroll
-                        for (int k = 0; k < ND; ++k) acc[i] += T(vb[int64_t(i) * ND * dg + k]) * x[ND * mm + k];
+                        for (int k = 0; k < ND; ++k) acc[i] += T(vb[int64_t(i) * ND * dg + k]) * input(ND * mm + k);
                 }
                 T sv;
                 if constexpr (ND == 3) sv = group32_sum3(acc[0], acc[1], acc[2], lane);
@@ -308,8 +469,20 @@ __global__ __launch_bounds__(kThreads, 4) void k_spmv_nodes(int64_t Nn, const in
                 if (beta != T(0)) out += beta * y[d];
                 __builtin_nontemporal_store(out, y + d);
             } else {
-                __builtin_nontemporal_store(sv, y + d);
-                const double wd = double(w0[d]);
+                T w;
+                if constexpr (GATHER == GATHER_X) {
+                    __builtin_nontemporal_store(sv, y + d);
+                    w = w0[d];
+                } else {  // these vectors are small and gathered again next: keep them cached
+                    y[d] = sv;
+                    w = input(d);
+                    gi.out[d] = w;
+                    if constexpr (GATHER == GATHER_BICG_P) {
+                        if (restart) gi.rh[d] = w;  // p = r = rhat
+                        else w = gi.rh[d];
+                    }
+                }
+                const double wd = double(w);
                 d0 += wd * double(sv);
                 if (MODE == 2) {
                     d1 += double(sv) * double(sv);
@@ -596,23 +769,8 @@ __global__ __launch_bounds__(kThreads) void k_cg_p_fused(int64_t N, const T *__r
                                                          const double *__restrict__ rz_partials, int rz_count,
                                                          KrylovScalars *sc, int it) {
     if (stopped(sc)) return;
-    double tot[2];
-    sum_partials<2>(rz_partials, rz_count, tot);
-    const double rho_prev = sc->rho_pp[it & 1];
-    const bool nan = !isfinite(tot[0]) || !isfinite(tot[1]);
-    const bool conv = !nan && tot[1] <= sc->tol2;
-    const double beta = tot[0] / rho_prev;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->rho_old = rho_prev;
-        sc->rho = tot[0];
-        sc->rho_pp[(it + 1) & 1] = tot[0];
-        sc->beta = beta;
-        sc->rnorm2 = tot[1];
-        sc->its = it + 1;
-        if (nan) sc->breakdown = 2;
-        else if (conv) sc->converged = 1;
-    }
-    if (nan || conv) return;
+    double beta;
+    if (!cg_p_scalars(rz_partials, rz_count, sc, it, beta)) return;
     const T bt = T(beta);
     using V = Vec16<T>;
     constexpr int W = V::W;
@@ -637,58 +795,6 @@ __global__ __launch_bounds__(kThreads) void k_cg_p_fused(int64_t N, const T *__r
 //              the (rhat, r), (r, r) partials for iteration i + 1.
 // The scalars of iteration i go to slot i & 1 (see KrylovScalars).
 
-// Finite-precision safeguards of the fused BiCGSTAB, for FP32 vectors.  Omega limit:
-// when t and s are nearly orthogonal (|(t, s)| < Omega |t| |s|), omega = (t, s) / (t, t)
-// is scaled up by Omega / cos(t, s), which keeps the BiCG coefficients of the next
-// steps accurate (Sleijpen and van der Vorst's 'limited omega', Omega = 0.7).  Restart
-// floor: see bicg_rho_floor.  Measured on the 5-step 100^3 and 200x100x100 neo-Hookean
-// solves: FP32 sweeps without the floor diverged on the larger one; the limit cut its
-// FP32 iterations by a third (27,704 against 41,951) but cost the FP64 vectors 48% more
-// (23,236 against 15,705), so FP64 runs plain BiCGSTAB.
-constexpr double kOmegaLimitF32 = 0.7;
-constexpr double kRhoFloorF32 = 1e-5;
-
-template <typename T>
-__device__ __forceinline__ double bicg_omega_limit() { return sizeof(T) == 4 ? kOmegaLimitF32 : 0.0; }
-
-struct BicgStart {
-    double rho, r2, rh2, rmin2;
-    bool nan, conv, div, restart;
-};
-
-// Restart floor of |(rhat, r)| / (|rhat| |r|): below it the shadow inner product has
-// lost its meaning.  In FP32 the vectors carry relative errors near 1e-7 that grow over
-// long solves, so the floor sits well above that noise; FP64 keeps the classic 1e-9.
-template <typename T>
-__device__ __forceinline__ double bicg_rho_floor() { return sizeof(T) == 4 ? kRhoFloorF32 : 1e-9; }
-
-// Tests at the start of iteration i (>= 1) from the partial sums tot = ((rhat, r), |r|^2)
-// of iteration i - 1: the same rules as the unfused finalize.
-__device__ BicgStart bicg_start(const double tot[2], const KrylovScalars *sc, int i, double rho_floor) {
-    const int q = (i - 1) & 1;
-    BicgStart b;
-    b.r2 = tot[1];
-    b.nan = !isfinite(tot[0]) || !isfinite(tot[1]);
-    b.conv = !b.nan && tot[1] <= sc->tol2;
-    b.div = !b.nan && !b.conv && tot[1] > 1e12 * sc->bnorm2;
-    const double rh2 = sc->rh2_pp[q], rmin2 = sc->rmin2_pp[q];
-    // (rhat, r) lost its size relative to |rhat||r|, omega vanished, or the residual
-    // grew 1000x above its best value: restart from the current r
-    b.restart = !(fabs(tot[0]) > rho_floor * sqrt(rh2 * tot[1])) || sc->omega_pp[q] == 0.0 || tot[1] > 1e6 * rmin2;
-    b.rho = b.restart ? tot[1] : tot[0];
-    b.rh2 = b.restart ? tot[1] : rh2;
-    b.rmin2 = fmin(rmin2, tot[1]);
-    return b;
-}
-
-__device__ __forceinline__ void bicg_publish_start(const BicgStart &b, KrylovScalars *sc, int i) {
-    sc->its = i;
-    sc->rnorm2 = b.r2;
-    if (b.nan) sc->breakdown = 2;
-    else if (b.conv) sc->converged = 1;
-    else if (b.div) sc->breakdown = 1;
-}
-
 // FOLD: the point-Jacobi scaling sits in the stored operator (K D^{-1}, see
 // k_scale_columns), so the SpMV inputs are p and s themselves and ph, sh are not written.
 template <typename T, bool FOLD = false>
@@ -699,27 +805,9 @@ __global__ __launch_bounds__(kThreads) void k_bicg_p_fused(int64_t N, int it, co
                                                            const double *__restrict__ xr_partials, int xr_count,
                                                            KrylovScalars *sc) {
     if (stopped(sc)) return;
-    bool restart = false;
-    double beta = 0.0, omega = 0.0;
-    if (it > 0) {
-        double tot[2];
-        sum_partials<2>(xr_partials, xr_count, tot);
-        const BicgStart b = bicg_start(tot, sc, it, bicg_rho_floor<T>());
-        const int q = (it - 1) & 1;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            bicg_publish_start(b, sc, it);
-            sc->rho_old = sc->rho_pp[q];
-            sc->rho = b.rho;
-            sc->rho_pp[it & 1] = b.rho;
-            sc->rh2_pp[it & 1] = b.rh2;
-            sc->rmin2_pp[it & 1] = b.rmin2;
-            if (b.restart) sc->restart_at = it;
-        }
-        if (b.nan || b.conv || b.div) return;
-        restart = b.restart;
-        omega = sc->omega_pp[q];
-        if (!restart) beta = (b.rho / sc->rho_pp[q]) * (sc->alpha_pp[q] / omega);
-    }
+    bool restart;
+    double beta, omega;
+    if (!bicg_p_scalars<T>(xr_partials, xr_count, sc, it, beta, omega, restart)) return;
     const T bt = T(beta), om = T(omega);
     using V = Vec16<T>;
     constexpr int W = V::W;
@@ -748,17 +836,8 @@ __global__ __launch_bounds__(kThreads) void k_bicg_s_fused(int64_t N, int it, co
                                                            const double *__restrict__ sp_partials, int sp_count,
                                                            KrylovScalars *sc) {
     if (stopped(sc)) return;
-    double tot[1];
-    sum_partials<1>(sp_partials, sp_count, tot);
-    if (!(tot[0] != 0.0) || !isfinite(tot[0])) {  // (rhat, v) vanished
-        if (blockIdx.x == 0 && threadIdx.x == 0) sc->breakdown = 1;
-        return;
-    }
-    const double alpha = sc->rho_pp[it & 1] / tot[0];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->alpha_pp[it & 1] = alpha;
-        sc->alpha = alpha;
-    }
+    double alpha;
+    if (!bicg_s_scalars(sp_partials, sp_count, sc, it, alpha)) return;
     const T al = T(alpha);
     using V = Vec16<T>;
     constexpr int W = V::W;
@@ -835,6 +914,20 @@ __global__ __launch_bounds__(kThreads) void k_bicg_check(int it, const double *_
     sum_partials<2>(xr_partials, xr_count, tot);
     const BicgStart b = bicg_start(tot, sc, it, rho_floor);
     if (threadIdx.x == 0) bicg_publish_start(b, sc, it);
+}
+
+// CG's convergence and NaN flags after iteration it - 1 when the next SpMV would take
+// them (one block; that SpMV repeats the test and publishes the other scalars).
+__global__ __launch_bounds__(kThreads) void k_cg_check(int it, const double *__restrict__ rz_partials, int rz_count,
+                                                       KrylovScalars *sc) {
+    if (stopped(sc) || it == 0) return;
+    double tot[2];
+    sum_partials<2>(rz_partials, rz_count, tot);
+    if (threadIdx.x != 0) return;
+    sc->its = it;
+    sc->rnorm2 = tot[1];
+    if (!isfinite(tot[0]) || !isfinite(tot[1])) sc->breakdown = 2;
+    else if (tot[1] <= sc->tol2) sc->converged = 1;
 }
 
 // ------------------------------------------------------------------ block Jacobi variants
@@ -1281,53 +1374,70 @@ void kry_cg_init(const fem_handle *h, const KrylovVecs<T> &k, const T *b, double
 
 // Launches the fused SpMV (partials into k.partials) and, unless the caller folds it
 // into its next kernel, the one-block finalize; returns the SpMV grid size.
-template <int ND, int MODE, typename T, typename TV = T>
+template <int ND, int MODE, typename T, typename TV = T, int GATHER = GATHER_X>
 static int kry_spmv_launch(const fem_handle *h, const T *x, T *y, const T *w0, const KrylovVecs<T> &k, int cg,
-                           const TV *values, bool finalize, hipStream_t s) {
+                           const TV *values, bool finalize, hipStream_t s, double *partials, GatherIn<T> gi) {
     const Graph &g = h->g;
     int G;
     if (k.layout == LAYOUT_SYM) {
-        if constexpr (std::is_same<T, TV>::value) {
+        if constexpr (std::is_same<T, TV>::value && GATHER == GATHER_X) {
             G = resident_grid(h, k_spmv_sym<ND, 4, MODE, T>);
             hipLaunchKernelGGL((k_spmv_sym<ND, 4, MODE, T>), dim3(G), dim3(kThreads), 0, s, g.Nn, g.node_ptr,
-                               g.up_base, g.node_nb, g.lo_val, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg);
+                               g.up_base, g.node_nb, g.lo_val, values, x, y, w0, T(1), T(0), partials, k.sc, cg);
         } else {
             throw Error(FEM_EINVAL, "the symmetric block layout takes values of the vector type");
         }
     } else if (g.node_dnb) {
         G = spmv_grid<ND, TV>(h);
-        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, true, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
-                           g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg,
-                           int(g.max_deg > kSpmvGroup));
+        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, true, TV, GATHER>), dim3(G), dim3(kThreads), 0, s, g.Nn,
+                           g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), partials, k.sc, cg,
+                           int(g.max_deg > kSpmvGroup), gi);
     } else {
         G = spmv_grid<ND, TV>(h);
-        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, false, TV>), dim3(G), dim3(kThreads), 0, s, g.Nn,
-                           g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), k.partials, k.sc, cg,
-                           int(g.max_deg > kSpmvGroup));
+        hipLaunchKernelGGL((k_spmv_nodes<ND, MODE, T, false, TV, GATHER>), dim3(G), dim3(kThreads), 0, s, g.Nn,
+                           g.node_ptr, g.node_nb, g.node_dnb, values, x, y, w0, T(1), T(0), partials, k.sc, cg,
+                           int(g.max_deg > kSpmvGroup), gi);
     }
     if (finalize) {
-        if (MODE == 1) hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kThreads), 0, s, G, k.partials, k.sc, cg);
-        else hipLaunchKernelGGL(k_fin_omega, dim3(1), dim3(kThreads), 0, s, G, k.partials, k.sc);
+        if (MODE == 1) hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kThreads), 0, s, G, partials, k.sc, cg);
+        else hipLaunchKernelGGL(k_fin_omega, dim3(1), dim3(kThreads), 0, s, G, partials, k.sc);
     }
     return G;
 }
 
 // The Krylov SpMV on the solve's operator: k.A, or the FP32 tangent k.A32 under FP64
 // vectors (products and sums in FP64).
-template <typename T, int MODE>
+template <typename T, int MODE, int GATHER = GATHER_X>
 static int kry_spmv(const fem_handle *h, const T *x, T *y, const T *w0, const KrylovVecs<T> &k, int cg,
-                    const T *values, hipStream_t s, bool finalize = true) {
+                    const T *values, hipStream_t s, bool finalize = true, double *partials = nullptr,
+                    GatherIn<T> gi = GatherIn<T>()) {
+    if (!partials) partials = k.partials;
     if constexpr (sizeof(T) == 8) {
         if (k.A32) {
             if (h->g.nd == 1)
-                return kry_spmv_launch<1, MODE, T, float>(h, x, y, w0, k, cg, k.A32,
-                                                                                     finalize, s);
-            return kry_spmv_launch<3, MODE, T, float>(h, x, y, w0, k, cg, k.A32, finalize,
-                                                                                 s);
+                return kry_spmv_launch<1, MODE, T, float, GATHER>(h, x, y, w0, k, cg, k.A32, finalize, s, partials, gi);
+            return kry_spmv_launch<3, MODE, T, float, GATHER>(h, x, y, w0, k, cg, k.A32, finalize, s, partials, gi);
         }
     }
-    if (h->g.nd == 1) return kry_spmv_launch<1, MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
-    return kry_spmv_launch<3, MODE, T>(h, x, y, w0, k, cg, values, finalize, s);
+    if (h->g.nd == 1)
+        return kry_spmv_launch<1, MODE, T, T, GATHER>(h, x, y, w0, k, cg, values, finalize, s, partials, gi);
+    return kry_spmv_launch<3, MODE, T, T, GATHER>(h, x, y, w0, k, cg, values, finalize, s, partials, gi);
+}
+
+// Whether an iteration forms p (and BiCGSTAB's s) inside the SpMV's gathers instead of in
+// vector kernels of their own.  Each formed vector saves a launch (3 to 6 us while the
+// vectors are small) and costs one or two more gathers per block, which grow with the
+// mesh.  Time per iteration, vector kernels -> gathers (3 dofs per node, FP64):
+//   CG (one more gather)         N = 27,783: 15.0 -> 12.0 us; 206,763: 32.7 -> 30.7; 680,943: 106 -> 114
+//   CG, FP32                     206,763: 22.8 -> 20.7; 680,943: 50.4 -> 49.3; 1,594,323: 130 -> 134
+//   BiCGSTAB (two and one more)  N = 27,783: 27.1 -> 20.9 us; 89,373: 37.8 -> 36.8; 206,763: 60.7 -> 63.7
+//   BiCGSTAB, FP32               27,783: 25.6 -> 20.7; 89,373: 31.5 -> 33.4
+// With one dof per node: CG N = 29,791: 16.2 -> 14.6, 226,981: 27.2 -> 29.0; BiCGSTAB
+// 29,791: 30.6 -> 27.1, 226,981: 53.8 -> 61.0.
+template <typename T>
+static bool krylov_gathers(const fem_handle *h, const KrylovVecs<T> &k, bool cg) {
+    const int64_t limit = cg ? (h->g.nd == 1 ? 100000 : 300000) : 60000;
+    return k.layout == LAYOUT_CSR && h->g.N <= limit;
 }
 
 template <typename T>
@@ -1376,6 +1486,37 @@ void kry_bicg_iter(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStrea
     if (!k.bj) {
         dim3 grid(krylov_vec_grid(h)), blk(kThreads);
         // folded Jacobi: the operator is K D^{-1} and the SpMVs take p and s directly
+        if (k.fold && krylov_gathers(h, k, false)) {
+            // three kernels; p and v alternate between two buffers each (ph and sh are free),
+            // since blocks still gather the old ones while others write the new
+            T *pb[2] = {k.p, k.ph}, *vb[2] = {k.v, k.sh};
+            const int o = it & 1, n = 1 - o;
+            double *sp = k.partials + krylov_grid(h);  // of the second SpMV, which reads the first one's
+            GatherIn<T> gi;
+            gi.b = pb[o];
+            gi.c = vb[o];
+            gi.out = pb[n];
+            gi.rh = k.rh;
+            gi.partials = k.partials2;
+            gi.count = int(grid.x);
+            gi.it = it;
+            if (ev) FEM_HIP(hipEventRecord(ev[0], s));
+            const int G1 = kry_spmv<T, 1, GATHER_BICG_P>(h, k.r, vb[n], nullptr, k, 0, A, s, false, k.partials, gi);
+            if (ev) FEM_HIP(hipEventRecord(ev[1], s));
+            GatherIn<T> gs;
+            gs.b = vb[n];
+            gs.out = k.s;
+            gs.partials = k.partials;
+            gs.count = G1;
+            gs.it = it;
+            if (ev) FEM_HIP(hipEventRecord(ev[2], s));
+            const int G2 = kry_spmv<T, 2, GATHER_BICG_S>(h, k.r, k.t, nullptr, k, 0, A, s, false, sp, gs);
+            if (ev) FEM_HIP(hipEventRecord(ev[3], s));
+            hipLaunchKernelGGL((k_bicg_xr_fused<T, true>), grid, blk, 0, s, N, it, k.x, k.r, k.rh, pb[n], k.s, k.s, k.t,
+                               sp, G2, k.partials2, k.sc);
+            FEM_HIP(hipGetLastError());
+            return;
+        }
         T *ph = k.fold ? k.p : k.ph, *sh = k.fold ? k.s : k.sh;
         if (k.fold)
             hipLaunchKernelGGL((k_bicg_p_fused<T, true>), grid, blk, 0, s, N, it, k.r, k.p, k.v, ph, k.rh, k.dinv,
@@ -1438,20 +1579,43 @@ void kry_cg_iter(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_
     const int64_t N = h->g.N;
     dim3 grid(krylov_vec_grid(h)), blk(kThreads);
     const T *A = k.A;
-    // slots: z = rh, q = v
+    // slots: z = rh, q = v; p alternates between two buffers when the SpMV forms it
+    const bool gathers = krylov_gathers(h, k, true);
+    T *p = k.p;
+    int G;
     if (ev) FEM_HIP(hipEventRecord(ev[0], s));
-    const int G = kry_spmv<T, 1>(h, k.p, k.v, k.p, k, 1, A, s, false);
+    if (gathers) {
+        T *pb[2] = {k.p, k.ph};
+        p = pb[1 - (it & 1)];
+        GatherIn<T> gi;
+        gi.b = pb[it & 1];
+        gi.out = p;
+        gi.partials = k.partials2;
+        gi.count = int(grid.x);
+        gi.it = it;
+        G = kry_spmv<T, 1, GATHER_CG_P>(h, k.rh, k.v, nullptr, k, 1, A, s, false, k.partials, gi);
+    } else {
+        G = kry_spmv<T, 1>(h, k.p, k.v, k.p, k, 1, A, s, false);
+    }
     if (ev) FEM_HIP(hipEventRecord(ev[1], s));
     if (!k.bj)
-        hipLaunchKernelGGL((k_cg_xr_fused<T>), grid, blk, 0, s, N, k.x, k.r, k.rh, k.p, k.v, k.dinv, k.partials, G,
+        hipLaunchKernelGGL((k_cg_xr_fused<T>), grid, blk, 0, s, N, k.x, k.r, k.rh, p, k.v, k.dinv, k.partials, G,
                            k.partials2, k.sc, it);
     else if (h->g.nd == 1)
-        hipLaunchKernelGGL((k_cg_xr_fused_bj<1, T>), grid, blk, 0, s, h->g.Nn, k.x, k.r, k.rh, k.p, k.v, k.dinv,
+        hipLaunchKernelGGL((k_cg_xr_fused_bj<1, T>), grid, blk, 0, s, h->g.Nn, k.x, k.r, k.rh, p, k.v, k.dinv,
                            k.partials, G, k.partials2, k.sc, it);
     else
-        hipLaunchKernelGGL((k_cg_xr_fused_bj<3, T>), grid, blk, 0, s, h->g.Nn, k.x, k.r, k.rh, k.p, k.v, k.dinv,
+        hipLaunchKernelGGL((k_cg_xr_fused_bj<3, T>), grid, blk, 0, s, h->g.Nn, k.x, k.r, k.rh, p, k.v, k.dinv,
                            k.partials, G, k.partials2, k.sc, it);
-    hipLaunchKernelGGL((k_cg_p_fused<T>), grid, blk, 0, s, N, k.rh, k.p, k.partials2, int(grid.x), k.sc, it);
+    if (!gathers)
+        hipLaunchKernelGGL((k_cg_p_fused<T>), grid, blk, 0, s, N, k.rh, k.p, k.partials2, int(grid.x), k.sc, it);
+    FEM_HIP(hipGetLastError());
+}
+
+template <typename T>
+void kry_cg_check(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_t s) {
+    if (!krylov_gathers(h, k, true)) return;  // the p kernel has tested already
+    hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(kThreads), 0, s, it, k.partials2, krylov_vec_grid(h), k.sc);
     FEM_HIP(hipGetLastError());
 }
 
@@ -1464,6 +1628,8 @@ template void kry_bicg_iter<float>(const fem_handle *, const KrylovVecs<float> &
 template void kry_bicg_iter<double>(const fem_handle *, const KrylovVecs<double> &, int, hipStream_t, hipEvent_t *);
 template void kry_bicg_check<float>(const fem_handle *, const KrylovVecs<float> &, int, hipStream_t);
 template void kry_bicg_check<double>(const fem_handle *, const KrylovVecs<double> &, int, hipStream_t);
+template void kry_cg_check<float>(const fem_handle *, const KrylovVecs<float> &, int, hipStream_t);
+template void kry_cg_check<double>(const fem_handle *, const KrylovVecs<double> &, int, hipStream_t);
 template int kry_spmv_q<float>(const fem_handle *, const KrylovVecs<float> &, hipStream_t);
 template int kry_spmv_q<double>(const fem_handle *, const KrylovVecs<double> &, hipStream_t);
 template void kry_cg_p_update<float>(const fem_handle *, const KrylovVecs<float> &, int, hipStream_t);

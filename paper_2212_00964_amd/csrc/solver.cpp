@@ -103,7 +103,7 @@ static void carve_solve(Carver &c, const fem_handle *h, SolveWork &w, bool need_
     w.ph = v[7];
     w.sh = v[8];
     w.dinv = v[9];
-    w.partials = c.take<double>(3 * int64_t(krylov_grid(h)));  // up to 3 sums per block
+    w.partials = c.take<double>(4 * int64_t(krylov_grid(h)));  // 1 sum per block, then up to 3
     w.partials2 = c.take<double>(3 * int64_t(krylov_grid(h)));
     w.norm_partials = c.take<double>(krylov_grid(h));
     w.sc = c.take<KrylovScalars>(1);
@@ -193,7 +193,8 @@ int krylov_solve(fem_handle *h, SolveWork &w, const T *A, const fem_solve_opts &
             else if (cg) kry_cg_iter<T>(h, k, it + j, s, e);
             else kry_bicg_iter<T>(h, k, it + j, s, e);
         }
-        if (!cg && !amg) kry_bicg_check<T>(h, k, it + every, s);
+        if (!cg) kry_bicg_check<T>(h, k, it + every, s);
+        else if (!amg) kry_cg_check<T>(h, k, it + every, s);
         FEM_HIP(hipMemcpyAsync(h->host_kry, w.sc, kScalarsHostBytes, hipMemcpyDeviceToHost, s));
         FEM_HIP(hipStreamSynchronize(s));
         std::memcpy(&hs, h->host_kry, kScalarsHostBytes);
