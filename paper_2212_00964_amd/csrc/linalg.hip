@@ -718,6 +718,21 @@ __global__ __launch_bounds__(kThreads) void k_cg_xr_fused(int64_t N, T *__restri
                                                           const T *__restrict__ q, const T *__restrict__ dinv,
                                                           const double *__restrict__ pq_partials, int pq_count,
                                                           double *partials, KrylovScalars *sc, int it) {
+    // 16-byte accesses over the bulk (the vectors are 256-byte aligned), scalar tail; the
+    // first ones go out before the partials are waited for
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W, stride = int64_t(gridDim.x) * kThreads;
+    int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    typename V::type xv{}, pv{}, rv{}, qv{}, dv{};
+    auto load = [&] {
+        xv = V::ld(x, i);
+        pv = V::ld(p, i);
+        rv = V::ld(r, i);
+        qv = V::ld(q, i);
+        dv = V::ld(dinv, i);
+    };
+    if (i < NV) load();
     if (stopped(sc)) return;
     double pq[1];
     sum_partials<1>(pq_partials, pq_count, pq);
@@ -738,12 +753,7 @@ __global__ __launch_bounds__(kThreads) void k_cg_xr_fused(int64_t N, T *__restri
         d0 += double(ri) * double(zi);
         d1 += double(ri) * double(ri);
     };
-    // 16-byte accesses over the bulk (the vectors are 256-byte aligned), scalar tail
-    using V = Vec16<T>;
-    constexpr int W = V::W;
-    const int64_t NV = N / W;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
-        typename V::type xv = V::ld(x, i), pv = V::ld(p, i), rv = V::ld(r, i), qv = V::ld(q, i), dv = V::ld(dinv, i);
+    while (i < NV) {
         xv += al * pv;
         rv -= al * qv;
         const typename V::type zv = dv * rv;
@@ -755,6 +765,8 @@ __global__ __launch_bounds__(kThreads) void k_cg_xr_fused(int64_t N, T *__restri
             d0 += double(rv[c]) * double(zv[c]);
             d1 += double(rv[c]) * double(rv[c]);
         }
+        i += stride;
+        if (i < NV) load();
     }
     if (blockIdx.x == 0)
         for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) update(i);
@@ -768,15 +780,25 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_cg_p_fused(int64_t N, const T *__restrict__ z, T *__restrict__ p,
                                                          const double *__restrict__ rz_partials, int rz_count,
                                                          KrylovScalars *sc, int it) {
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W, stride = int64_t(gridDim.x) * kThreads;
+    int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    typename V::type zv{}, pv{};
+    auto load = [&] {
+        zv = V::ld(z, i);
+        pv = V::ld(p, i);
+    };
+    if (i < NV) load();
     if (stopped(sc)) return;
     double beta;
     if (!cg_p_scalars(rz_partials, rz_count, sc, it, beta)) return;
     const T bt = T(beta);
-    using V = Vec16<T>;
-    constexpr int W = V::W;
-    const int64_t NV = N / W;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads)
-        V::st_nt(p, i, V::ld(z, i) + bt * V::ld(p, i));
+    while (i < NV) {
+        V::st_nt(p, i, zv + bt * pv);
+        i += stride;
+        if (i < NV) load();
+    }
     if (blockIdx.x == 0)
         for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) p[i] = z[i] + bt * p[i];
 }
@@ -804,20 +826,29 @@ __global__ __launch_bounds__(kThreads) void k_bicg_p_fused(int64_t N, int it, co
                                                            const T *__restrict__ dinv,
                                                            const double *__restrict__ xr_partials, int xr_count,
                                                            KrylovScalars *sc) {
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W, stride = int64_t(gridDim.x) * kThreads;
+    int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    typename V::type rv{}, po{}, vo{};
+    auto load = [&] {
+        rv = V::ld(r, i);
+        po = V::ld(p, i);
+        vo = V::ld(v, i);
+    };
+    if (i < NV) load();
     if (stopped(sc)) return;
     bool restart;
     double beta, omega;
     if (!bicg_p_scalars<T>(xr_partials, xr_count, sc, it, beta, omega, restart)) return;
     const T bt = T(beta), om = T(omega);
-    using V = Vec16<T>;
-    constexpr int W = V::W;
-    const int64_t NV = N / W;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
-        const typename V::type rv = V::ld(r, i);
-        const typename V::type pv = restart ? rv : rv + bt * (V::ld(p, i) - om * V::ld(v, i));
+    while (i < NV) {
+        const typename V::type pv = restart ? rv : rv + bt * (po - om * vo);
         V::st(p, i, pv);
         if (!FOLD) V::st(ph, i, V::ld(dinv, i) * pv);
         if (restart) V::st(rh, i, rv);
+        i += stride;
+        if (i < NV) load();
     }
     if (blockIdx.x == 0)
         for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) {
@@ -835,17 +866,26 @@ __global__ __launch_bounds__(kThreads) void k_bicg_s_fused(int64_t N, int it, co
                                                            T *__restrict__ sh, const T *__restrict__ dinv,
                                                            const double *__restrict__ sp_partials, int sp_count,
                                                            KrylovScalars *sc) {
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W, stride = int64_t(gridDim.x) * kThreads;
+    int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    typename V::type rv{}, vv{};
+    auto load = [&] {
+        rv = V::ld(r, i);
+        vv = V::ld(v, i);
+    };
+    if (i < NV) load();
     if (stopped(sc)) return;
     double alpha;
     if (!bicg_s_scalars(sp_partials, sp_count, sc, it, alpha)) return;
     const T al = T(alpha);
-    using V = Vec16<T>;
-    constexpr int W = V::W;
-    const int64_t NV = N / W;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
-        const typename V::type sv = V::ld(r, i) - al * V::ld(v, i);
+    while (i < NV) {
+        const typename V::type sv = rv - al * vv;
         V::st(s, i, sv);
         if (!FOLD) V::st(sh, i, V::ld(dinv, i) * sv);
+        i += stride;
+        if (i < NV) load();
     }
     if (blockIdx.x == 0)
         for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) {
@@ -862,6 +902,19 @@ __global__ __launch_bounds__(kThreads) void k_bicg_xr_fused(int64_t N, int it, T
                                                             const T *__restrict__ t,
                                                             const double *__restrict__ sp_partials, int sp_count,
                                                             double *xr_partials, KrylovScalars *sc) {
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W, stride = int64_t(gridDim.x) * kThreads;
+    int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
+    typename V::type sv{}, xv{}, pv{}, tv{}, hv{};
+    auto load = [&] {
+        sv = V::ld(s, i);
+        xv = V::ld(x, i);
+        pv = V::ld(ph, i);
+        tv = V::ld(t, i);
+        hv = V::ld(rh, i);
+    };
+    if (i < NV) load();
     if (stopped(sc)) return;
     double tot[3];  // (t, s), (t, t), (s, s)
     sum_partials<3>(sp_partials, sp_count, tot);
@@ -877,20 +930,17 @@ __global__ __launch_bounds__(kThreads) void k_bicg_xr_fused(int64_t N, int it, T
     }
     const T al = T(sc->alpha_pp[it & 1]), om = T(omega);
     double d0 = 0.0, d1 = 0.0;
-    using V = Vec16<T>;
-    constexpr int W = V::W;
-    const int64_t NV = N / W;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
-        const typename V::type sv = V::ld(s, i);
-        V::st(x, i, V::ld(x, i) + al * V::ld(ph, i) + om * (FOLD ? sv : V::ld(sh, i)));
-        const typename V::type rv = sv - om * V::ld(t, i);
-        const typename V::type hv = V::ld(rh, i);
+    while (i < NV) {
+        V::st(x, i, xv + al * pv + om * (FOLD ? sv : V::ld(sh, i)));
+        const typename V::type rv = sv - om * tv;
         V::st(r, i, rv);
 #pragma unroll
         for (int c = 0; c < W; ++c) {
             d0 += double(hv[c]) * double(rv[c]);
             d1 += double(rv[c]) * double(rv[c]);
         }
+        i += stride;
+        if (i < NV) load();
     }
     if (blockIdx.x == 0)
         for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) {
