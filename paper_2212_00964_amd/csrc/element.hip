@@ -2,12 +2,9 @@
 //
 // Work mapping: one element per group of 8 consecutive lanes, lane a <-> local
 // node a (so a 64-wide wavefront holds 8 elements and every cross-lane exchange
-// stays inside a wavefront).  At each of the 2x2x2 Gauss points the lanes of an
-// element build the isoparametric Jacobian and the displacement gradient by an
-// 8-lane butterfly sum (every lane ends with bit-identical values), then each lane
-// forms the quantities of its own node.  For the tangent, each lane accumulates the
-// 3 x 24 row block of K_e that belongs to its node; the shape-gradient data of the
-// other seven nodes come from LDS.
+// stays inside a wavefront); per-point work is done once per Gauss point, lane q <->
+// point q, and handed on through LDS.  The tangent's row blocks take two lanes per node
+// (k_tangent_blocks).
 //
 // Element outputs go to a per-element scratch area and are summed per node / per
 // CSR block by separate gather kernels: every global entry is written exactly once,
@@ -328,20 +325,42 @@ __device__ __forceinline__ ElemIds elem_ids(int64_t Ne) {
 // relative to local node 0 of the element, in FP64 before rounding to T: the
 // gradients are unchanged (the shape-function gradients sum to zero) but the
 // differences of nearby absolute values no longer cancel in T arithmetic.
-template <int ND, typename T>
+// All loads go out before the first is used; what is read is fixed at compile time (a test
+// of the pointers between the loads made every component wait for the one before it).
+enum : int { LOAD_COORDS = 0, LOAD_FIELD = 1, LOAD_REL = 2, LOAD_MASKED = 4 };  // the field; minus node 0's; 0 where masked
+template <int ND, int FLAGS, typename T>
 __device__ __forceinline__ void load_node(const double *coords, const int32_t *conn, const double *u,
-                                          const uint8_t *mask, const ElemIds &id, T X[3], T U[ND], bool rel_u) {
+                                          const uint8_t *mask, const ElemIds &id, T X[3], T U[ND]) {
+    constexpr bool kField = FLAGS & LOAD_FIELD, kRel = FLAGS & LOAD_REL, kMask = FLAGS & LOAD_MASKED;
     const int64_t n = conn[id.e * 8 + id.a];
     const int64_t n0 = conn[id.e * 8];
+    double x[3], x0[3], v[ND], v0[ND];
+    uint8_t m[ND], m0[ND];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) X[i] = T(coords[3 * n + i] - coords[3 * n0 + i]);
+    for (int i = 0; i < 3; ++i) {
+        x[i] = coords[3 * n + i];
+        x0[i] = coords[3 * n0 + i];
+    }
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-        const int64_t d = ND * n + i, d0 = ND * n0 + i;
-        const double ua = (u == nullptr || (mask && mask[d])) ? 0.0 : u[d];
-        const double u0 = (!rel_u || u == nullptr || (mask && mask[d0])) ? 0.0 : u[d0];
-        U[i] = T(ua - u0);
+        v[i] = kField ? u[ND * n + i] : 0.0;
+        v0[i] = kField && kRel ? u[ND * n0 + i] : 0.0;
+        m[i] = kMask ? mask[ND * n + i] : 0;
+        m0[i] = kMask && kRel ? mask[ND * n0 + i] : 0;
     }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) X[i] = T(x[i] - x0[i]);
+#pragma unroll
+    for (int i = 0; i < ND; ++i) U[i] = T((m[i] ? 0.0 : v[i]) - (m0[i] ? 0.0 : v0[i]));
+}
+
+// Hand-off of LDS data between lanes of one wavefront: a wavefront's LDS operations are
+// performed in program order, so a lane reads what other lanes of its wavefront wrote
+// before this point; the fence (wavefront scope) and the wave barrier keep the compiler
+// from moving LDS accesses across it.  Neither emits an instruction.
+__device__ __forceinline__ void wave_lds_handoff() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ------------------------------------------------------------------ residual-type kernels
@@ -376,9 +395,10 @@ __global__ __launch_bounds__(kThreads) void k_element_vec(int64_t Ne, const doub
         // its Newton iterations were measured to converge with this form's rounding.
         ElemIds id = elem_ids(Ne);
         double X[3], U[ND], W[ND];
-        load_node<ND, double>(coords, conn, u, nullptr, id, X, U, true);
+        load_node<ND, LOAD_FIELD | LOAD_REL>(coords, conn, u, nullptr, id, X, U);
         if (MODE != VEC_RESIDUAL)
-            load_node<ND, double>(coords, conn, v, MODE == VEC_LIFT ? nullptr : mask, id, X, W, MODE != VEC_VJP);
+            load_node<ND, LOAD_FIELD | (MODE == VEC_LIFT ? 0 : LOAD_MASKED) | (MODE != VEC_VJP ? LOAD_REL : 0)>(
+                coords, conn, v, mask, id, X, W);
         double th = theta[id.e];
         double mod = (MODE == VEC_VJP) ? 1.0 : modulus(mat, th);
         double acc[3] = {0, 0, 0};
@@ -418,9 +438,10 @@ __global__ __launch_bounds__(kThreads) void k_element_vec(int64_t Ne, const doub
     __shared__ double Ms[kElemsPerBlock][8][9];
     ElemIds id = elem_ids(Ne);
     double X[3], U[ND], W[ND];
-    load_node<ND, double>(coords, conn, u, nullptr, id, X, U, true);
+    load_node<ND, LOAD_FIELD | LOAD_REL>(coords, conn, u, nullptr, id, X, U);
     if (MODE != VEC_RESIDUAL)
-        load_node<ND, double>(coords, conn, v, MODE == VEC_LIFT ? nullptr : mask, id, X, W, MODE != VEC_VJP);
+        load_node<ND, LOAD_FIELD | (MODE == VEC_LIFT ? 0 : LOAD_MASKED) | (MODE != VEC_VJP ? LOAD_REL : 0)>(
+                coords, conn, v, mask, id, X, W);
     double *mine = nodes[id.el][id.a];
 #pragma unroll
     for (int i = 0; i < 3; ++i) mine[i] = X[i];
@@ -510,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void k_element_mass(int64_t Ne, const dou
                                                            int *status) {
     ElemIds id = elem_ids(Ne);
     double X[3], Xv[ND];
-    load_node<ND, double>(coords, conn, x, nullptr, id, X, Xv, false);
+    load_node<ND, LOAD_FIELD>(coords, conn, x, nullptr, id, X, Xv);
     const double gq = 0.57735026918962576451;
     double acc[ND];
 #pragma unroll
@@ -545,7 +566,7 @@ __global__ __launch_bounds__(kThreads) void k_j2_commit(int64_t Ne, const double
                                                        const double *__restrict__ u, double *__restrict__ hist) {
     ElemIds id = elem_ids(Ne);
     double X[3], U[3];
-    load_node<3, double>(coords, conn, u, nullptr, id, X, U, true);
+    load_node<3, LOAD_FIELD | LOAD_REL>(coords, conn, u, nullptr, id, X, U);
     double Gm[3][3] = {};
 #pragma unroll 1
     for (int q = 0; q < 8; ++q) {
@@ -578,7 +599,7 @@ __global__ __launch_bounds__(kThreads) void k_j2_average(int64_t Ne, const doubl
     __shared__ double red[kThreads / 64][7];
     ElemIds id = elem_ids(Ne);
     double X[3], U[1];
-    load_node<1, double>(coords, conn, nullptr, nullptr, id, X, U, false);
+    load_node<1, LOAD_COORDS>(coords, conn, nullptr, nullptr, id, X, U);
     double w = 0.0;
 #pragma unroll 1
     for (int q = 0; q < 8; ++q) {
@@ -655,7 +676,7 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 2) void k_element_ta
     __shared__ T lds[kElemsPerBlock * ES];
     ElemIds id = elem_ids(Ne);
     T X[3], U[ND];
-    load_node<ND, T>(coords, conn, kNonlinear ? u : nullptr, nullptr, id, X, U, true);
+    load_node<ND, kNonlinear ? LOAD_FIELD | LOAD_REL : LOAD_COORDS>(coords, conn, u, nullptr, id, X, U);
     T mod = T(modulus(mat, theta[id.e]));
     T K[8][ND][ND];
 #pragma unroll
@@ -896,131 +917,455 @@ __global__ __launch_bounds__(256) void k_extract_binv(int64_t Nn, const int64_t 
     if (!invert_block<ND>(B, binv + int64_t(ND) * ND * n)) atomicOr(status, ST_NAN);
 }
 
-// Node-centric gather (one wavefront per node, for node degrees up to
-// kGatherMaxDeg): the node's element row blocks are one contiguous run of slots
-// ne_ptr[n] .. ne_ptr[n+1]-1 (element ascending); each slot's 8 column blocks are
-// added into an LDS image of the node's rows at the positions tgt gives, one slot at
-// a time (so every entry sums its contributions in element order, and no two lanes
-// touch the same entry in a step).  The rows are then written once, coalesced, with
-// the symmetric Dirichlet elimination applied, and the Jacobi inverse diagonal of the
-// node is taken from the same image.
-constexpr int kGatherMaxDeg = 32;
-constexpr int kGatherSlots = 8;  // slots preloaded per pass
+// ------------------------------------------------------------------ tangent by rows
+// The tangent of meshes whose nodes have at most 8 elements and 32 neighbours.  At a
+// Gauss point every law here gives
+//   K_e[(a,i),(b,k)] = sum_q sum_r C_ikr(a, q) dN_b,r(q),
+//   C_ikr = P_i H_kr + R_i F_kr + Q_k H_ir + delta_ik (M dN_a)_r
+// with dN the reference gradients, H, F, M matrices of the point (pulled back to the
+// reference cube by J^{-T}) and P, Q, R vectors of node a, quadrature weight included:
+//   neo-Hookean: H = F^{-T} J^{-T}, F = F J^{-T}, h = H dN_a, f = F dN_a,
+//                P = aw h - c23 f, Q = bw h, R = -c23 h, M = cw J^{-1} J^{-T}
+//   J2:          H = J^{-T}, F = s J^{-T}, P = lw h, Q = mw h, R = -bw f, M = mw J^{-1} J^{-T}
+//   linear:      as J2 without F
+//   Poisson:     M only.
+// k_tangent_blocks: a wavefront takes 8 (FP32) or 4 (FP64) elements; lane q evaluates
+// Gauss point q once and leaves those numbers (28 at most) in LDS; then 16 lanes per
+// element, two per node a (one for each half q2 of the points), sum C over the rule's
+// factors -- dN_b,0 does not depend on q0, dN_b,1 not on q1, dN_b,2 not on q2 up to its
+// sign, so 8 running sums per entry (i, k) hold what the 8 columns b need -- contract
+// them with the one-dimensional shape values once and write the slot's row block, rows
+// i one after the other.  Exchanges stay inside the wavefront: no block barrier.
+// What bounds it: at 100^3 in FP32 the 2.4 GB it writes (878 us; 595 us when its stores
+// stay in L2; 272 M vector instructions, 0.44 ms at full issue).  The element matrices
+// with 8 lanes per element and all exchanges of a point through LDS and block barriers
+// took 1,129 us.  FP64, 37x29x23 neo-Hookean: 86 -> 53 us, two rounds of wavefronts each
+// waiting on the chain of divisions and the cube root of its points.
+// Whole tangent, element kernel and gather, before -> now: 100^3 FP32 2,097 -> 1,537 us
+// (linear 1,864 -> 1,442, Poisson 1,037 -> 385), FP64 3,849 -> 2,992 (Poisson 1,310 ->
+// 564); 40^3 FP32 156 -> 88, FP64 317 -> 226.
+template <int MODEL>
+constexpr int state_size() {
+    return MODEL == FEM_POISSON ? 8 : (MODEL == FEM_LINEAR_ELASTIC ? 20 : 28);
+}
+// Elements per wavefront, and the rows i that a lane sums at a time: FP64 takes them one by
+// one (24 running sums in 48 registers; all 72 would leave one wavefront per SIMD).
+template <typename T>
+constexpr int wave_elems() { return sizeof(T) == 4 ? 8 : 4; }
+template <int ND, typename T>
+constexpr int rows_at_once() { return sizeof(T) == 4 ? ND : 1; }
 
-// Hand-off of LDS data between lanes of one wavefront: a wavefront's LDS operations are
-// performed in program order, so a lane reads what other lanes of its wavefront wrote
-// before this point; the fence (wavefront scope) and the wave barrier keep the compiler
-// from moving LDS accesses across it.  Neither emits an instruction.
-__device__ __forceinline__ void wave_lds_handoff() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+template <int MODEL, int ND, typename T>
+__global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_blocks(
+    int64_t Ne, const double *__restrict__ coords, const int32_t *__restrict__ conn,
+    const int32_t *__restrict__ kpos, Material mat, const double *__restrict__ theta, const double *__restrict__ u,
+    const double *__restrict__ hist, T *__restrict__ ke, int *status) {
+    constexpr bool kNonlinear = MODEL == FEM_NEO_HOOKEAN || MODEL == FEM_J2_PLASTIC;
+    constexpr int NF = 3 + (kNonlinear ? ND : 0), BS = ND * ND, S = state_size<MODEL>(), W = 16 / int(sizeof(T));
+    constexpr int E = wave_elems<T>(), RI = rows_at_once<ND, T>(), RS = RI * ND;
+    constexpr int kLds = E * 8 * S > 64 * NF ? E * 8 * S : 64 * NF;
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    // the nodes' values, then the points' numbers; and one row i of 32 slots on its way out
+    constexpr int kRow = 8 * ND, kOut = ND == 1 ? 0 : 32 * kRow;
+    __shared__ __align__(16) T lds[kThreads / 64][kLds + kOut];
+    __shared__ int32_t skpos[kThreads / 64][E * 8];
+    const int wave = threadIdx.x / 64, lane = threadIdx.x & 63;
+    // Blocks of one XCD take adjacent elements: the slots of a node that share cache lines are
+    // then completed in one L2 instead of leaving it as partial lines.
+    const int64_t blk = int64_t(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const int64_t ew = (blk * (kThreads / 64) + wave) * E;  // first element of the wavefront
+    if (ew >= Ne) return;  // wave-uniform; there are no block barriers
+    T *node_vals = lds[wave];
+    {
+        // lanes past the wavefront's or the mesh's elements repeat one and store nothing
+        const int el = (lane >> 3) % E;
+        const bool valid = lane < 8 * E && ew + el < Ne;
+        ElemIds id;
+        id.a = lane & 7;
+        id.el = el;
+        id.valid = valid;
+        id.e = ew + el < Ne ? ew + el : Ne - 1;
+        const int64_t e = id.e;
+        const int q = id.a;
+        T X[3], U[ND];
+        load_node<ND, kNonlinear ? LOAD_FIELD | LOAD_REL : LOAD_COORDS>(coords, conn, u, nullptr, id, X, U);
+        const T mod = T(modulus(mat, theta[e]));
+#pragma unroll
+        for (int i = 0; i < 3; ++i) node_vals[lane * NF + i] = X[i];
+        if constexpr (kNonlinear)
+#pragma unroll
+            for (int i = 0; i < ND; ++i) node_vals[lane * NF + 3 + i] = U[i];
+        // (the slots too, before the first store: a load after one would wait for it)
+        if (lane < 8 * E) skpos[wave][lane] = valid ? kpos[e * 8 + id.a] : -1;
+        wave_lds_handoff();
+        T J[3][3] = {}, Gr[3][3] = {};
+#pragma unroll 2
+        for (int b = 0; b < 8; ++b) {
+            T dN[3];
+            ref_grad<T>(b, q, dN);
+            const T *nb = node_vals + (lane - q + b) * NF;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    J[i][j] = fma(nb[i], dN[j], J[i][j]);
+                    if constexpr (kNonlinear) Gr[i][j] = fma(nb[3 + i], dN[j], Gr[i][j]);
+                }
+        }
+        const T d = det3(J);
+        bool mat_ok = true;
+        T B[3][3];  // J^{-T}
+        inv_transpose3(J, d, B);
+        // Weight of the point with the factors common to all columns b: every 1-D shape value
+        // below is taken relative to the larger one, lp = (1 + 1/sqrt(3)) / 2.
+        const T wq = T(0.5 * 0.78867513459481288225 * 0.78867513459481288225) * d;
+        T out[S];
+#pragma unroll
+        for (int c = 0; c < S; ++c) out[c] = T(0);
+        auto put_metric = [&](int at, T w) {  // w J^{-1} J^{-T}: (00, 11, 22, 12, 02, 01)
+            constexpr int pr[6][2] = {{0, 0}, {1, 1}, {2, 2}, {1, 2}, {0, 2}, {0, 1}};
+#pragma unroll
+            for (int c = 0; c < 6; ++c) {
+                const int r = pr[c][0], t = pr[c][1];
+                out[at + c] = w * (B[0][r] * B[0][t] + B[1][r] * B[1][t] + B[2][r] * B[2][t]);
+            }
+        };
+        auto put_matrix = [&](int at, const T A[3][3]) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) out[at + 3 * i + r] = A[i][r];
+        };
+        auto times_b = [&](const T A[3][3], T R[3][3]) {  // A J^{-T}
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) R[i][r] = A[i][0] * B[0][r] + A[i][1] * B[1][r] + A[i][2] * B[2][r];
+        };
+        T G[3][3];
+        if constexpr (kNonlinear)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) G[i][j] = Gr[i][0] * B[j][0] + Gr[i][1] * B[j][1] + Gr[i][2] * B[j][2];
+        // The third reference axis reversed where q2 = 0: columns b2 = 0 then enter with the same
+        // sign as b2 = 1.
+#pragma unroll
+        for (int i = 0; i < 3; ++i) B[i][2] = (q & 4) ? B[i][2] : -B[i][2];
+        if constexpr (MODEL == FEM_NEO_HOOKEAN) {
+            NHState<T> st;
+            mat_ok = nh_state(G, mod, T(mat.bulk_ratio), st);
+            T R[3][3];
+            times_b(st.H, R);
+            put_matrix(0, R);
+            const T cw = wq * st.c, c23 = T(2.0 / 3.0) * cw;
+            times_b(st.F, R);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) R[i][r] *= c23;
+            put_matrix(9, R);
+            put_metric(18, cw);
+            out[24] = wq * st.alpha;
+            out[25] = wq * st.beta;
+        } else if constexpr (MODEL == FEM_J2_PLASTIC) {
+            J2State<T> st;
+            j2_state(mat, mod, G, hist + (e * 8 + q) * 12, st);
+            put_matrix(0, B);
+            const T D[3][3] = {{st.dev[0], st.dev[5], st.dev[4]}, {st.dev[5], st.dev[1], st.dev[3]},
+                               {st.dev[4], st.dev[3], st.dev[2]}};
+            T R[3][3];
+            times_b(D, R);
+            put_matrix(9, R);
+            put_metric(18, wq * st.mup);
+            out[24] = wq * st.lw;
+            out[25] = wq * st.mup;
+            out[26] = wq * st.beta;
+        } else if constexpr (MODEL == FEM_LINEAR_ELASTIC) {
+            const T nu = T(mat.nu);
+            const T lw = wq * mod * nu / ((T(1) + nu) * (T(1) - T(2) * nu)), mw = wq * mod / (T(2) * (T(1) + nu));
+            put_matrix(0, B);
+            put_metric(9, mw);
+            out[15] = lw;
+            out[16] = mw;
+        } else {
+            put_metric(0, wq * mod);
+        }
+        if (valid && (!(d > T(0)) || !mat_ok))
+            atomicOr(status, (!(d > T(0)) ? ST_MESH : 0) | (!mat_ok ? ST_INVERTED : 0));
+        wave_lds_handoff();  // the nodes' values are read
+        if (lane < 8 * E) {
+            vec *dst = reinterpret_cast<vec *>(lds[wave] + lane * S);
+#pragma unroll
+            for (int c = 0; c < S / W; ++c) {
+                vec v;
+#pragma unroll
+                for (int w = 0; w < W; ++w) v[w] = out[c * W + w];
+                dst[c] = v;
+            }
+        }
+        wave_lds_handoff();
+    }
+    const int half = lane & 1, a = (lane >> 1) & 7;
+    const T lp = T(0.78867513459481288225), lm = T(0.21132486540518711775);  // (1 +- 1/sqrt(3)) / 2
+    const bool ax = (a ^ (a >> 1)) & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
+    // the sign of dN_a,2 goes with the reversed axis
+    const T hx = ax ? T(0.5) : T(-0.5), hy = ay ? T(0.5) : T(-0.5), hz = (az == bool(half)) ? T(0.5) : T(-0.5);
+    const T l2 = (az == bool(half)) ? lp : lm, t = lm / lp;
+#pragma unroll 1
+    for (int round = 0; round < E / 4; ++round) {
+        const int el = 4 * round + (lane >> 4);
+        const bool valid = ew + el < Ne;
+        int at = (el * 8 + 4 * half) * S;
+#pragma unroll
+        for (int i0 = 0; i0 < ND; i0 += RI) {
+            // (an opaque offset: the numbers are read from LDS again for each group of rows
+            // instead of being carried along in registers)
+            asm volatile("" : "+v"(at));
+            const T *pt = lds[wave] + at;
+            T S0[2][RS], S1[2][RS], S2[2][2][RS];
+#pragma unroll
+            for (int q1 = 0; q1 < 2; ++q1)
+#pragma unroll
+                for (int q0 = 0; q0 < 2; ++q0) {
+                    const T *st = pt + (2 * q1 + q0) * S;
+                    const T l0 = (ax == bool(q0)) ? lp : lm, l1 = (ay == bool(q1)) ? lp : lm;
+                    const T dN[3] = {hx * l1 * l2, hy * l0 * l2, hz * l0 * l1};
+                    constexpr int kM = MODEL == FEM_POISSON ? 0 : (MODEL == FEM_LINEAR_ELASTIC ? 9 : 18);
+                    const T *M = st + kM;
+                    const T gb[3] = {M[0] * dN[0] + M[5] * dN[1] + M[4] * dN[2],
+                                     M[5] * dN[0] + M[1] * dN[1] + M[3] * dN[2],
+                                     M[4] * dN[0] + M[3] * dN[1] + M[2] * dN[2]};
+                    // the running sums of the three directions, as the start of this point's terms
+                    auto start = [&](int ik, int r) -> T {
+                        if (r == 0) return q0 == 0 ? T(0) : S0[q1][ik];
+                        if (r == 1) return q1 == 0 ? T(0) : S1[q0][ik];
+                        return T(0);
+                    };
+                    auto put = [&](int ik, int r, T v) {
+                        if (r == 0) S0[q1][ik] = v;
+                        else if (r == 1) S1[q0][ik] = v;
+                        else S2[q0][q1][ik] = v;
+                    };
+                    if constexpr (MODEL == FEM_POISSON) {
+#pragma unroll
+                        for (int r = 0; r < 3; ++r) put(0, r, start(0, r) + gb[r]);
+                    } else {
+                        constexpr bool kF = MODEL != FEM_LINEAR_ELASTIC;
+                        const T *H = st, *F = st + 9;
+                        T h[3], Q[3];
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            h[i] = H[3 * i] * dN[0] + H[3 * i + 1] * dN[1] + H[3 * i + 2] * dN[2];
+                            Q[i] = st[MODEL == FEM_LINEAR_ELASTIC ? 16 : 25] * h[i];
+                        }
+#pragma unroll
+                        for (int c = 0; c < RI; ++c) {
+                            const int i = RI == ND ? c : i0;
+                            const T *Hi = H + 3 * i, *Fi = F + 3 * i;
+                            const T fi = kF ? Fi[0] * dN[0] + Fi[1] * dN[1] + Fi[2] * dN[2] : T(0);
+                            T P, R = T(0);
+                            if constexpr (MODEL == FEM_NEO_HOOKEAN) {
+                                P = st[24] * h[i] - fi;
+                                R = -h[i];
+                            } else if constexpr (MODEL == FEM_J2_PLASTIC) {
+                                P = st[24] * h[i];
+                                R = -st[26] * fi;
+                            } else {
+                                P = st[15] * h[i];
+                            }
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                                for (int r = 0; r < 3; ++r) {
+                                    T v = start(3 * c + k, r);
+                                    if (k == i) v += gb[r];
+                                    v = fma(P, H[3 * k + r], v);
+                                    if constexpr (kF) v = fma(R, F[3 * k + r], v);
+                                    put(3 * c + k, r, fma(Q[k], Hi[r], v));
+                                }
+                        }
+                    }
+                }
+            // Columns b = (b0, b1, b2): dN_b,0 = s0 l_b1 l_b2 / 2 and so on; with every l over lp (1 or
+            // t) and lp^2 / 2 in the weights, half h adds l_b2(h) A + B to column b, where
+            //   A[b0][b1] = s0 sum_q1 l_b1 S0 + s1 sum_q0 l_b0 S1,  B[b0][b1] = sum l_b0 l_b1 S2
+            // for b2 = h, and l_b2(h) A - B for the other.  Lane h keeps b2 = h and hands its part
+            // of the other to its neighbour.  Nodes in HEX8 order: (b0, b1) = 00, 10, 11, 01.
+#pragma unroll
+            for (int c = 0; c < RI; ++c) {
+                T o[4 * ND];
+#pragma unroll
+                for (int k = 0; k < ND; ++k) {
+                    const int ik = c * ND + k;
+                    const T u0 = fma(t, S0[1][ik], S0[0][ik]), u1 = fma(t, S0[0][ik], S0[1][ik]);
+                    const T w0 = fma(t, S1[1][ik], S1[0][ik]), w1 = fma(t, S1[0][ik], S1[1][ik]);
+                    const T v00 = fma(t, S2[1][0][ik], S2[0][0][ik]), v10 = fma(t, S2[0][0][ik], S2[1][0][ik]);
+                    const T v01 = fma(t, S2[1][1][ik], S2[0][1][ik]), v11 = fma(t, S2[0][1][ik], S2[1][1][ik]);
+                    const T A[4] = {-u0 - w0, u0 - w1, u1 + w1, w0 - u1};
+                    const T B[4] = {fma(t, v01, v00), fma(t, v11, v10), fma(t, v10, v11), fma(t, v00, v01)};
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        o[b * ND + k] = (A[b] + B[b]) + dpp_read<kDppXor1>(fma(t, A[b], -B[b]));
+                }
+                // Row i of a slot is 8 * ND consecutive values.  The wavefront's 32 rows go through
+                // LDS so that neighbouring lanes store neighbouring 16-byte pieces (stored straight
+                // from each lane's registers they took as long again as the whole kernel).
+                if constexpr (kOut == 0) {
+                    if (valid) {
+                        T *row = ke + int64_t(skpos[wave][32 * round + (lane >> 1)]) * 8 * BS + half * 4;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) row[v] = o[v];
+                    }
+                } else {
+                    T *stage = lds[wave] + kLds;
+#pragma unroll
+                    for (int v = 0; v < 4 * ND / W; ++v) {
+                        vec x;
+#pragma unroll
+                        for (int w = 0; w < W; ++w) x[w] = o[v * W + w];
+                        reinterpret_cast<vec *>(stage + lane * 4 * ND)[v] = x;
+                    }
+                    wave_lds_handoff();
+                    constexpr int kP = kRow / W;  // pieces per row
+#pragma unroll
+                    for (int t = 0; t < 32 * kP / 64; ++t) {
+                        const int p = lane + 64 * t, sl = p / kP;
+                        const int32_t k = skpos[wave][32 * round + sl];
+                        const vec x = reinterpret_cast<const vec *>(stage)[p];
+                        if (k >= 0)
+                            reinterpret_cast<vec *>(ke + int64_t(k) * 8 * BS + (i0 + c) * kRow)[p - sl * kP] = x;
+                    }
+                    wave_lds_handoff();  // before the next row is staged
+                }
+            }
+        }
+    }
 }
 
+constexpr int kGatherMaxDeg = 32;  // neighbours of a node on the row path
+constexpr int kGatherMaxInc = 8;   // and its elements
+
+// The rows of two consecutive nodes per wavefront, 32 lanes each.  The slots of a node
+// (and of the next one) are one contiguous run of k_tangent_blocks' output: the wavefront
+// copies it to LDS, lane j of a half sums what belongs to neighbour block j -- a 64-bit
+// mask per block (bit 8 * slot + b), built from the slots' target bytes, lists its
+// contributions in element order -- applies the symmetric Dirichlet elimination and
+// writes each CSR value once, with the node's Jacobi diagonal or block inverse.  No
+// read-modify-write of an image and no block barrier.
+// What bounds it: at 100^3 in FP32 its 2.3 GB in and 1.0 GB out, 5.1 TB/s (650 us; slot by
+// slot additions into an LDS image of the rows took 1,079 us); FP64, 37x29x23: 39 -> 28 us.
 template <int ND, int LAYOUT, typename T>
-__global__ __launch_bounds__(256) void k_gather_node(int64_t Nn, const int64_t *__restrict__ node_ptr,
-                                                     const uint8_t *__restrict__ nb_bits,
-                                                     const int64_t *__restrict__ ne_ptr,
-                                                     const uint8_t *__restrict__ tgt,
-                                                     const int64_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ bdiag,
-                                                     const int64_t *__restrict__ up_base,
-                                                     const uint8_t *__restrict__ mask, const T *__restrict__ ke,
-                                                     T *__restrict__ values, T *__restrict__ dinv, int bj,
-                                                     int *status) {
-    constexpr int BS = ND * ND;
-    constexpr int W = 64;
-    constexpr int PER = (8 * BS + W - 1) / W;  // values of one slot per lane
-    __shared__ T img[256 / W][kGatherMaxDeg * BS];
-    __shared__ uint8_t nbm[256 / W][kGatherMaxDeg];  // Dirichlet bits of each neighbour's dofs
-    // wavefront index made explicitly uniform, so node and slot indices live in scalar
-    // registers and their loads go through the scalar cache
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / W), lane = threadIdx.x % W;
-    T *a = img[wave];
-    // Each wavefront walks nodes with a grid stride (a few resident blocks per CU;
-    // one short-lived workgroup per node would be bound by the dispatch rate).  The
-    // loop trip count is uniform per wavefront and the kernel has no block barriers.
-    for (int64_t n = int64_t(blockIdx.x) * (256 / W) + wave; n < Nn; n += int64_t(gridDim.x) * (256 / W)) {
-        const int64_t nb0 = node_ptr[n];
-        const int deg = int(node_ptr[n + 1] - nb0);
-        // Dirichlet bits of the node's own dofs and of its neighbours', fetched up front so
-        // their latency overlaps the value loads
-        int rowbits = 0;
-        if (mask)
+__global__ __launch_bounds__(kThreads) void k_gather_rows(int64_t Nn, const int64_t *__restrict__ node_ptr,
+                                                          const uint8_t *__restrict__ nb_bits,
+                                                          const int64_t *__restrict__ ne_ptr,
+                                                          const uint8_t *__restrict__ tgt,
+                                                          const int32_t *__restrict__ bdiag,
+                                                          const int64_t *__restrict__ up_base,
+                                                          const uint8_t *__restrict__ mask, const T *__restrict__ ke,
+                                                          T *__restrict__ values, T *__restrict__ dinv, int bj,
+                                                          int *status) {
+    constexpr int BS = ND * ND, W = 16 / int(sizeof(T)), kSlot = 8 * BS;
+    constexpr int kMaxT = 2 * kGatherMaxInc * kSlot;            // values of a pair of nodes
+    constexpr int kPieces = (kMaxT / W + 63) / 64;              // 16-byte pieces per lane
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    __shared__ __align__(16) T run[kThreads / 64][kMaxT];
+    __shared__ unsigned long long mset[kThreads / 32][kGatherMaxDeg];
+    const int wave = threadIdx.x / 64, lane64 = threadIdx.x & 63, lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
+    const int64_t n0 = (int64_t(blockIdx.x) * (kThreads / 64) + wave) * 2;
+    if (n0 >= Nn) return;  // wave-uniform; there are no block barriers
+    const int64_t k0 = ne_ptr[n0], kmid = ne_ptr[n0 + 1], k1 = n0 + 1 < Nn ? ne_ptr[n0 + 2] : kmid;
+    const int pieces = int(k1 - k0) * kSlot / W;
+    const vec *src = reinterpret_cast<const vec *>(ke + k0 * kSlot);
+    vec buf[kPieces];
 #pragma unroll
-            for (int c = 0; c < ND; ++c) rowbits |= int(mask[ND * n + c] != 0) << c;
-        if (lane < deg) nbm[wave][lane] = nb_bits[nb0 + lane];
-        for (int l = lane; l < deg * BS; l += W) a[l] = T(0);
-        wave_lds_handoff();  // the zeroed image and the neighbour bits, to every lane
-        const int64_t k1 = ne_ptr[n + 1];
-        for (int64_t k0 = ne_ptr[n]; k0 < k1; k0 += kGatherSlots) {
-            T val[kGatherSlots][PER];
-            int pos[kGatherSlots][PER];
+    for (int t = 0; t < kPieces; ++t) {
+        const int i = lane64 + 64 * t;
+        buf[t] = src[i < pieces ? i : 0];
+    }
+    // this half's node; the second half of an odd last pair idles on the first one
+    const bool live = n0 + (grp & 1) < Nn;
+    const int64_t n = live ? n0 + (grp & 1) : n0;
+    const int64_t kn = live && (grp & 1) ? kmid : k0;
+    const int pairs = 8 * int((live && (grp & 1) ? k1 : kmid) - kn);
+    const int64_t nb0 = node_ptr[n];
+    const int deg = int(node_ptr[n + 1] - nb0), jd = int(bdiag[n] - nb0);
+    const bool act = lane < deg;
+    const int colbits = nb_bits[nb0 + (act ? lane : 0)];
+    int rowbits = 0;
+    if (mask)
 #pragma unroll
-            for (int kk = 0; kk < kGatherSlots; ++kk) {
-                // the slot index is uniform across the wavefront, so its 8 targets come in
-                // one scalar load; the value loads are unconditional (clamped indices) so
-                // no load sits behind a branch that would wait for everything in flight
-                const bool slot_ok = k0 + kk < k1;
-                const int64_t k = slot_ok ? k0 + kk : k0;
-                const uint64_t tw = *reinterpret_cast<const uint64_t *>(tgt + k * 8);
+        for (int c = 0; c < ND; ++c) rowbits |= int(mask[ND * n + c] != 0) << c;
+    const int t0 = tgt[kn * 8 + (lane < pairs ? lane : 0)], t1 = tgt[kn * 8 + (lane + 32 < pairs ? lane + 32 : 0)];
+    mset[grp][lane] = 0;
+    wave_lds_handoff();
+    if (lane < pairs) atomicOr(&mset[grp][t0], 1ull << lane);
+    if (lane + 32 < pairs) atomicOr(&mset[grp][t1], 1ull << (lane + 32));
 #pragma unroll
-                for (int t = 0; t < PER; ++t) {
-                    const int l = lane + W * t;
-                    const bool ok = slot_ok && l < 8 * BS;
-                    const int lc = l < 8 * BS ? l : 0;
-                    const int b = lc / BS;
-                    val[kk][t] = ke[(k * 8) * BS + lc];
-                    const int j = int((tw >> (8 * b)) & 0xff);
-                    pos[kk][t] = ok ? j * BS + (lc - b * BS) : -1;
-                }
-            }
-            // slot by slot: within a slot no two lanes touch one entry; a later slot's
-            // read-modify-write of an entry follows the earlier slot's
+    for (int t = 0; t < kPieces; ++t)
+        if (lane64 + 64 * t < pieces) reinterpret_cast<vec *>(run[wave])[lane64 + 64 * t] = buf[t];
+    wave_lds_handoff();
+    unsigned long long m = act ? mset[grp][lane] : 0;
+    // the diagonal block has twice as many contributions as any other of a structured
+    // mesh: a free lane takes those of its last four slots
+    const bool split = deg < 32;
+    if (split) {
+        if (lane == jd) m &= 0xffffffffull;
+        else if (lane == 31) m = mset[grp][jd] & ~0xffffffffull;
+    }
+    T acc[BS];
 #pragma unroll
-            for (int kk = 0; kk < kGatherSlots; ++kk) {
+    for (int c = 0; c < BS; ++c) acc[c] = T(0);
+    const T *mine = run[wave] + (kn - k0) * kSlot;
+    while (m) {  // ascending slots: element order
+        const int l = __builtin_ctzll(m);
+        m &= m - 1;
+        const T *o = mine + (l >> 3) * kSlot + (l & 7) * ND;
 #pragma unroll
-                for (int t = 0; t < PER; ++t)
-                    if (pos[kk][t] >= 0) a[pos[kk][t]] += val[kk][t];
-                wave_lds_handoff();
-            }
+        for (int i = 0; i < ND; ++i)
+#pragma unroll
+            for (int c = 0; c < ND; ++c) acc[i * ND + c] += o[i * 8 * ND + c];
+    }
+    if (split)
+#pragma unroll
+        for (int c = 0; c < BS; ++c) {
+            const T up = __shfl(acc[c], 31, 32);
+            if (lane == jd) acc[c] += up;
         }
-        // rows of the node, CSR (or upper blocks only), with the Dirichlet elimination
-        const int jd = int(bdiag[n] - nb0);
-        wave_lds_handoff();
-        bool bad = false;
+    if (!act || !live) return;
+    bool bad = false;
 #pragma unroll
-        for (int i = 0; i < ND; ++i) {
-            const int64_t rbase = (LAYOUT == LAYOUT_SYM) ? 0 : row_ptr[ND * n + i];
-            const bool rm = (rowbits >> i) & 1;
-            for (int r = lane; r < ND * deg; r += W) {
-                const int j = r / ND, c = r - j * ND;
-                T v = a[j * BS + i * ND + c];
-                if (rm || ((nbm[wave][j] >> c) & 1)) v = (j == jd && c == i) ? T(1) : T(0);
-                bad |= !isfinite(v);
-                if (LAYOUT == LAYOUT_SYM) {
-                    if (j >= jd) values[int64_t(BS) * (up_base[n] + j - jd) + i * ND + c] = v;
-                } else {
-                    values[rbase + r] = v;
-                }
+    for (int i = 0; i < ND; ++i)
+#pragma unroll
+        for (int c = 0; c < ND; ++c) {
+            if (((rowbits >> i) | (colbits >> c)) & 1) acc[i * ND + c] = (lane == jd && i == c) ? T(1) : T(0);
+            bad |= !isfinite(acc[i * ND + c]);
+        }
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+        T *dst = (LAYOUT == LAYOUT_SYM) ? values + int64_t(BS) * (up_base[n] + lane - jd) + i * ND
+                                        : values + int64_t(BS) * nb0 + int64_t(i) * ND * deg + ND * lane;
+        if (LAYOUT != LAYOUT_SYM || lane >= jd)
+#pragma unroll
+            for (int c = 0; c < ND; ++c) dst[c] = acc[i * ND + c];
+    }
+    if (dinv && lane == jd) {
+        if (!bj) {
+#pragma unroll
+            for (int c = 0; c < ND; ++c) {
+                bad |= !(acc[c * ND + c] != T(0));
+                dinv[ND * n + c] = T(1) / acc[c * ND + c];
             }
-        }
-        if (dinv && !bj && lane < ND) {
-            T v = ((rowbits >> lane) & 1) ? T(1) : a[jd * BS + lane * ND + lane];
-            bad |= !(v != T(0)) || !isfinite(v);
-            dinv[ND * n + lane] = T(1) / v;
-        }
-        if (dinv && bj && lane == 0) {
+        } else {
             double B[ND][ND];
 #pragma unroll
             for (int i = 0; i < ND; ++i)
 #pragma unroll
-                for (int c = 0; c < ND; ++c)
-                    B[i][c] = (((rowbits >> i) | (rowbits >> c)) & 1) ? (i == c ? 1.0 : 0.0) : double(a[jd * BS + i * ND + c]);
+                for (int c = 0; c < ND; ++c) B[i][c] = double(acc[i * ND + c]);
             bad |= !invert_block<ND>(B, dinv + int64_t(BS) * n);
         }
-        if (bad) atomicOr(status, ST_NAN);
-        wave_lds_handoff();  // the next node reuses the image
     }
+    if (bad) atomicOr(status, ST_NAN);
 }
 
 template <int ND, int LAYOUT, typename T>
@@ -1041,11 +1386,6 @@ __global__ __launch_bounds__(256) void k_extract_dinv(int64_t N, const int64_t *
 }
 
 inline unsigned grid_for(int64_t n, int threads) { return unsigned((n + threads - 1) / threads); }
-
-// Resident grid of the node-centric gather: 8 blocks of 4 wavefronts per CU.
-inline unsigned gather_grid(const fem_handle *h) {
-    return unsigned(std::min<int64_t>(int64_t(8) * h->num_cus, (h->g.Nn + 3) / 4));
-}
 
 }  // namespace
 
@@ -1174,21 +1514,27 @@ void launch_tangent(const fem_handle *h, const double *u, const double *theta, T
     const int bj = precond == FEM_PRECOND_BLOCK_JACOBI;
     const Graph &g = h->g;
     if (g.Ne == 0) return;
-    unsigned gridE = grid_for(g.Ne, kElemsPerBlock);
-    const bool node_gather = g.tgt != nullptr && g.max_deg <= kGatherMaxDeg;
+    // Nodes beyond 8 elements or 32 neighbours (fans, irregular block corners) do not fit
+    // the row gather's masks and lanes: element matrices and the per-block gather.
+    const bool by_rows = g.tgt != nullptr && g.max_deg <= kGatherMaxDeg && g.max_inc <= kGatherMaxInc;
     FEM_DISPATCH_MODEL(h, {
-        hipLaunchKernelGGL((k_element_tangent<MODEL, ND, T>), dim3(gridE), dim3(kThreads), 0, s, g.Ne, h->m.coords,
-                           h->m.conn, g.kpos, h->mat, theta, u, h->hist, ke, h->status);
-        if (node_gather) {
+        if (by_rows) {
+            hipLaunchKernelGGL((k_tangent_blocks<MODEL, ND, T>),
+                               dim3((grid_for(g.Ne, wave_elems<T>() * kThreads / 64) + 7) / 8 * 8), dim3(kThreads), 0,
+                               s, g.Ne, h->m.coords, h->m.conn, g.kpos, h->mat, theta, u, h->hist,
+                               ke, h->status);
+            const dim3 grid(grid_for(g.Nn, 2 * kThreads / 64));
             if (layout == LAYOUT_SYM)
-                hipLaunchKernelGGL((k_gather_node<ND, LAYOUT_SYM, T>), dim3(gather_grid(h)), dim3(256), 0, s,
-                                   g.Nn, g.node_ptr, g.nb_bits, g.ne_ptr, g.tgt, g.row_ptr, g.bdiag, g.up_base,
-                                   h->m.mask, ke, values, dinv, bj, h->status);
+                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_SYM, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
+                                   g.nb_bits, g.ne_ptr, g.tgt, g.bdiag, g.up_base, h->m.mask, ke, values, dinv, bj,
+                                   h->status);
             else
-                hipLaunchKernelGGL((k_gather_node<ND, LAYOUT_CSR, T>), dim3(gather_grid(h)), dim3(256), 0, s,
-                                   g.Nn, g.node_ptr, g.nb_bits, g.ne_ptr, g.tgt, g.row_ptr, g.bdiag, g.up_base,
-                                   h->m.mask, ke, values, dinv, bj, h->status);
+                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_CSR, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
+                                   g.nb_bits, g.ne_ptr, g.tgt, g.bdiag, g.up_base, h->m.mask, ke, values, dinv, bj,
+                                   h->status);
         } else {
+            hipLaunchKernelGGL((k_element_tangent<MODEL, ND, T>), dim3(grid_for(g.Ne, kElemsPerBlock)), dim3(kThreads),
+                               0, s, g.Ne, h->m.coords, h->m.conn, g.kpos, h->mat, theta, u, h->hist, ke, h->status);
             if (layout == LAYOUT_SYM)
                 hipLaunchKernelGGL((k_gather_values<ND, LAYOUT_SYM, T>), dim3(grid_for(g.nnzb * ND, 256)), dim3(256),
                                    0, s, g.nnzb, g.node_ptr, g.node_nb, g.blk_row, g.blk_ptr, g.blk_src, g.row_ptr,
@@ -1200,7 +1546,7 @@ void launch_tangent(const fem_handle *h, const double *u, const double *theta, T
         }
     });
     FEM_HIP(hipGetLastError());
-    if (dinv && !node_gather) {
+    if (dinv && !by_rows) {
         if (!bj) {
             launch_extract_dinv<T>(h, values, dinv, s, layout);
         } else {

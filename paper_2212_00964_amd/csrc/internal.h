@@ -89,6 +89,7 @@ struct Graph {
     uint8_t *tgt = nullptr;       // [Ne*64] for slot k and column block b: the block's position
                                   //         in the row node's neighbour list (max_deg <= 255)
     int max_deg = 0;              // largest node degree of the node graph
+    int max_inc = 0;              // most elements of one node
     int64_t *row_ptr = nullptr;   // [N+1] scalar CSR row starts
     // Symmetric block layout: only blocks (n, m) with m >= n are stored, block-major
     // (nd x nd, row-major), in CSR order of the node graph.
@@ -175,7 +176,7 @@ namespace fem {
 // uploads it into the handle's Graph (same array meanings).
 struct HostGraph {
     int64_t Nn = 0, Ne = 0, N = 0, nnz = 0, nnzb = 0, nnzb_up = 0;
-    int nd = 1, max_deg = 0;
+    int nd = 1, max_deg = 0, max_inc = 0;
     std::vector<int64_t> ne_ptr, node_ptr, blk_ptr, row_ptr, up_base;
     std::vector<int32_t> kpos, node_nb, blk_row, mirror, bdiag, bslot, blk_src, lo_val;
     std::vector<int16_t> dnb;  // empty when some neighbour offset needs more than 16 bits

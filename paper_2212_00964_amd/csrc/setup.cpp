@@ -137,6 +137,7 @@ HostGraph host_graph(const fem_mesh_desc *d, const std::vector<uint8_t> &mask) {
     int64_t max_deg = 0;
     for (int64_t n = 0; n < Nn; ++n) max_deg = std::max(max_deg, node_ptr[n + 1] - node_ptr[n]);
     g.max_deg = int(max_deg);
+    for (int64_t n = 0; n < Nn; ++n) g.max_inc = std::max(g.max_inc, int(ne_ptr[n + 1] - ne_ptr[n]));
     std::vector<uint8_t> &tgt = g.tgt;
     if (max_deg <= 255) {
         tgt.resize(Ne * 64);
@@ -217,6 +218,7 @@ void build_graph(fem_handle *h, const fem_mesh_desc *d) {
     g.nnzb = hg.nnzb;
     g.nnzb_up = hg.nnzb_up;
     g.max_deg = hg.max_deg;
+    g.max_inc = hg.max_inc;
     g.up_base = upload(h, hg.up_base);
     g.lo_val = upload(h, hg.lo_val);
     g.node_ptr = upload(h, hg.node_ptr);

@@ -1,0 +1,65 @@
+"""Edges of the kernels' tiles and of the rules that choose between them, against the oracle.
+
+Tolerances as in test_gpu_parity.py: FP64 assembly 1e-13, FP32 tangent 2e-6, J2 1e-12 / 1e-5
+(its returned stress divides by the von Mises norm), solves 1e-10.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from paper_2212_00964_amd import inputs as gen
+from parity import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+fem = pytest.importorskip("paper_2212_00964_amd.fem")
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.detach().cpu().numpy()
+
+
+def _line(law, nx, ny=1, nz=1):
+    if law == "poisson":
+        coords, conn = gen.box_mesh(nx, ny, nz)
+        mask = np.zeros(coords.shape[0], np.uint8)
+        mask[0] = 1
+        return gen.Problem(name="line", coords=coords, conn=conn, ndpn=1, model=gen.POISSON,
+                           theta=gen.lognormal_field(conn.shape[0], 0.0, 0.3, 1), dirichlet_mask=mask,
+                           dirichlet_values=np.zeros(coords.shape[0]))
+    if law == "linear":
+        return gen.cantilever(nx, ny, nz, distort_seed=3)
+    return gen.nh_tensile(nx, ny, nz, seed=2, distort_seed=3)
+
+
+# element counts around the 4 and 8 elements of a wavefront and the 16 and 32 of a block;
+# node counts 4 (n + 1) around the two nodes of a wavefront and the eight of a block
+@pytest.mark.parametrize("law", ["poisson", "linear", "nh"])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 9, 15, 17, 31, 32, 33, 65])
+def test_tangent_at_tile_edges(law, n):
+    for shape in ((n, 1, 1), (2, n, 1)):
+        p = _line(law, *shape)
+        u = 0.002 * np.random.default_rng(n).standard_normal(p.n_dofs)
+        r_ref, K_ref = orc.assemble(p, orc.Pattern(p), u, F=orc.load_vector(p))
+        prob = fem.Problem(p, DEV)
+        r, K = prob.assemble(u)
+        assert_parity(host(r), r_ref, 1e-13, f"{law} {shape} residual")
+        assert_parity(host(K), K_ref, 1e-13, f"{law} {shape} FP64")
+        _, K32 = prob.assemble(u, residual=False, values_dtype=torch.float32)
+        assert_parity(host(K32), K_ref, 2e-6, f"{law} {shape} FP32")
+        _, Ks = prob.assemble(u, residual=False, layout=fem.LAYOUT_SYM_BLOCK)
+        x = np.random.default_rng(n + 1).standard_normal(p.n_dofs)
+        y = prob.spmv(Ks, torch.as_tensor(x, device=DEV), layout=fem.LAYOUT_SYM_BLOCK)
+        y_ref = prob.spmv(K, torch.as_tensor(x, device=DEV))
+        assert_parity(host(y), host(y_ref), 1e-13, f"{law} {shape} symmetric blocks")
+        prob.close()
