@@ -127,36 +127,97 @@ __global__ __launch_bounds__(kThreads) void k_amg_cdinv(int64_t na, const int64_
     cdinv[t] = T(1) / cvals[(cdiag[I] * NC + k) * NC + k];
 }
 
-// y = alpha A_c x, one thread per coarse row (I, k).
-template <int NC, typename T>
-__global__ __launch_bounds__(kThreads) void k_amg_cspmv(int64_t na, const int64_t *__restrict__ cptr,
-                                                        const int32_t *__restrict__ ccol,
-                                                        const T *__restrict__ cvals, const T *__restrict__ x,
-                                                        T *__restrict__ y, T alpha, const KrylovScalars *sc) {
-    if (halted(sc)) return;
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (t >= na * NC) return;
-    const int64_t I = t / NC;
-    const int k = int(t - I * NC);
-    T s = T(0);
-    for (int64_t b = cptr[I]; b < cptr[I + 1]; ++b) {
-        const T *row = cvals + (b * NC + k) * NC;
-        const T *xj = x + int64_t(ccol[b]) * NC;
-#pragma unroll
-        for (int l = 0; l < NC; ++l) s += row[l] * xj[l];
+// Coarse block rows, one wavefront per aggregate I: lane (bb, k) sums row k of blocks bb,
+// bb + LPR, ... (neighbouring lanes read neighbouring rows of a block), three blocks of
+// every lane in flight, and the lanes of a row meet in LDS.
+//   STEP = false: y = alpha A_c x
+//   STEP = true:  one Chebyshev step in the same kernel, with x the direction d:
+//                 rc -= A_c d, y = c1 d + c2 dinv rc (the next direction), z += y
+// What bounds it: latency (a 64^3 mesh has 10,648 rows, 1.3 per resident wavefront, and
+// 38 MB of FP32 blocks from the Infinity Cache): a step takes 11.3 us; one thread per row
+// took 15.0 us and the vector update of the step another 4.8 us.  (Two aggregates per
+// wavefront with six blocks in flight per lane: 12.0 us.)
+template <int NC, bool STEP, typename T>
+__global__ __launch_bounds__(kThreads) void k_amg_rows(int64_t na, const int64_t *__restrict__ cptr,
+                                                       const int32_t *__restrict__ ccol,
+                                                       const T *__restrict__ cvals, const T *__restrict__ x,
+                                                       T *__restrict__ y, T alpha, T *__restrict__ rc,
+                                                       T *__restrict__ z, const T *__restrict__ dinv, T c1, T c2,
+                                                       const KrylovScalars *sc) {
+    constexpr int LPR = 64 / NC;  // lanes of a row
+    constexpr int U = 3;          // blocks in flight per lane
+    __shared__ T part[kWavesPerBlock][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // blocks of one XCD take adjacent rows, the same ones in every step
+    const int64_t I = (int64_t(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) * kWavesPerBlock + wave;
+    if (I >= na) return;  // wave-uniform; there are no block barriers
+    const int bb = lane / NC, k = lane - bb * NC;
+    const int64_t b0 = cptr[I];
+    const int nb = int(cptr[I + 1] - b0);
+    const int64_t own = I * NC + (lane < NC ? lane : 0);
+    T r0 = T(0), d0 = T(0), z0 = T(0), di0 = T(0);
+    if constexpr (STEP) {
+        r0 = rc[own];
+        d0 = x[own];
+        z0 = z[own];
+        di0 = dinv[own];
     }
-    y[t] = alpha * s;
+    if (halted(sc)) return;
+    T s = T(0);
+    for (int base = 0; base < nb; base += U * LPR) {
+        T row[U][NC], xj[U][NC];
+        int32_t J[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int b = base + t * LPR + bb;
+            const bool in = bb < LPR && b < nb;
+            const int64_t bl = b0 + (in ? b : 0);  // clamped: the loads are branch-free
+            J[t] = ccol[bl];
+#pragma unroll
+            for (int l = 0; l < NC; ++l) row[t][l] = in ? cvals[(bl * NC + k) * NC + l] : T(0);
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+#pragma unroll
+            for (int l = 0; l < NC; ++l) xj[t][l] = x[int64_t(J[t]) * NC + l];
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+#pragma unroll
+            for (int l = 0; l < NC; ++l) s += row[t][l] * xj[t][l];
+    }
+    if constexpr (NC == 1) {
+        s = wave_sum(s);
+    } else {
+        part[wave][lane] = s;
+        wave_lds_handoff();
+        s = T(0);
+        if (lane < NC)
+#pragma unroll
+            for (int q = 0; q < LPR; ++q) s += part[wave][q * NC + lane];
+    }
+    if (lane >= NC) return;
+    if constexpr (STEP) {
+        const T ri = r0 - s;
+        rc[own] = ri;
+        const T d = c1 * d0 + c2 * di0 * ri;
+        y[own] = d;
+        z[own] = z0 + d;
+    } else {
+        y[own] = alpha * s;
+    }
 }
 
 // ------------------------------------------------------------------ grid transfers
-// bc[I] = sum over the nodes i of aggregate I of P_i^T (r_i - w_i); one wavefront per
+// rc[I] = sum over the nodes i of aggregate I of P_i^T (r_i - w_i), and the first step of
+// the coarse Chebyshev iteration from 0, d = z = dinv rc / theta; one wavefront per
 // aggregate.
 template <int ND, int NC, typename T>
 __global__ __launch_bounds__(kThreads) void k_amg_restrict(int64_t na, const int64_t *__restrict__ agg_ptr,
                                                            const int32_t *__restrict__ agg_nodes,
                                                            const T *__restrict__ P, const T *__restrict__ r,
-                                                           const T *__restrict__ w, T *__restrict__ bc,
-                                                           const KrylovScalars *sc) {
+                                                           const T *__restrict__ w, const T *__restrict__ cdinv,
+                                                           T inv_theta, T *__restrict__ rc, T *__restrict__ d,
+                                                           T *__restrict__ z, const KrylovScalars *sc) {
     if (halted(sc)) return;
     const int64_t I = int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -176,7 +237,12 @@ __global__ __launch_bounds__(kThreads) void k_amg_restrict(int64_t na, const int
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
         const T v = wave_sum(acc[k]);
-        if (lane == 0) bc[I * NC + k] = v;
+        if (lane == 0) {
+            const T di = cdinv[I * NC + k] * v * inv_theta;
+            rc[I * NC + k] = v;
+            d[I * NC + k] = di;
+            z[I * NC + k] = di;
+        }
     }
 }
 
@@ -337,18 +403,19 @@ __global__ __launch_bounds__(kThreads) void k_power_scale(int64_t n, T *__restri
 }
 
 // ------------------------------------------------------------------ preconditioned CG pieces
-// alpha = rho_pp[it & 1] / (p, q); x += alpha p; r -= alpha q.
+// alpha = rho_pp[it & 1] / (p, q); x += alpha p; r -= alpha q; and with z the first
+// pre-smoothing step of the V-cycle on the new residual, z = dinv r / theta.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_cg_xr_plain(int64_t N, T *__restrict__ x, T *__restrict__ r,
                                                           const T *__restrict__ p, const T *__restrict__ q,
                                                           const double *__restrict__ pq_partials, int pq_count,
-                                                          KrylovScalars *sc, int it) {
+                                                          KrylovScalars *sc, int it, T *__restrict__ z,
+                                                          const T *__restrict__ dinv, T inv_theta) {
     if (halted(sc)) return;
     __shared__ double red[kWavesPerBlock];
     double t = 0.0;
     for (int b = threadIdx.x; b < pq_count; b += kThreads) t += pq_partials[b];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    t = wave_sum(t);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
     __syncthreads();
     double pq = 0.0;
@@ -360,29 +427,62 @@ __global__ __launch_bounds__(kThreads) void k_cg_xr_plain(int64_t N, T *__restri
     const double alpha = sc->rho_pp[it & 1] / pq;
     if (blockIdx.x == 0 && threadIdx.x == 0) sc->alpha = alpha;
     const T al = T(alpha);
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < N; i += int64_t(gridDim.x) * kThreads) {
-        x[i] += al * p[i];
-        r[i] -= al * q[i];
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W;
+    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
+        V::st(x, i, V::ld(x, i) + al * V::ld(p, i));
+        const typename V::type rv = V::ld(r, i) - al * V::ld(q, i);
+        V::st(r, i, rv);
+        if (z) V::st(z, i, V::ld(dinv, i) * rv * inv_theta);
     }
+    if (blockIdx.x == 0)
+        for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) {
+            x[i] += al * p[i];
+            const T ri = r[i] - al * q[i];
+            r[i] = ri;
+            if (z) z[i] = dinv[i] * ri * inv_theta;
+        }
 }
 
-// Block partials of (r, z) and (r, r), partials[b] and partials[G + b].
+// Block partials of (r, z) and (r, r), partials[b] and partials[G + b].  With w = A z: the
+// last post-smoothing step first, z += dinv (r - w) / theta (partials may be null).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_dot_rz_rr(int64_t N, const T *__restrict__ r, const T *__restrict__ z,
-                                                        double *partials, const KrylovScalars *sc) {
+__global__ __launch_bounds__(kThreads) void k_dot_rz_rr(int64_t N, const T *__restrict__ r, T *__restrict__ z,
+                                                        const T *__restrict__ w, const T *__restrict__ dinv,
+                                                        T inv_theta, double *partials, const KrylovScalars *sc) {
     if (halted(sc)) return;
     __shared__ double red[kWavesPerBlock][2];
     double a = 0.0, b = 0.0;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < N; i += int64_t(gridDim.x) * kThreads) {
-        const double ri = double(r[i]);
-        a += ri * double(z[i]);
-        b += ri * ri;
-    }
+    using V = Vec16<T>;
+    constexpr int W = V::W;
+    const int64_t NV = N / W;
+    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < NV; i += int64_t(gridDim.x) * kThreads) {
+        const typename V::type rv = V::ld(r, i);
+        typename V::type zv = V::ld(z, i);
+        if (w) {
+            zv += V::ld(dinv, i) * (rv - V::ld(w, i)) * inv_theta;
+            V::st(z, i, zv);
+        }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, 64);
-        b += __shfl_xor(b, o, 64);
+        for (int c = 0; c < W; ++c) {
+            a += double(rv[c]) * double(zv[c]);
+            b += double(rv[c]) * double(rv[c]);
+        }
     }
+    if (blockIdx.x == 0)
+        for (int64_t i = NV * W + threadIdx.x; i < N; i += kThreads) {
+            T zi = z[i];
+            if (w) {
+                zi += dinv[i] * (r[i] - w[i]) * inv_theta;
+                z[i] = zi;
+            }
+            a += double(r[i]) * double(zi);
+            b += double(r[i]) * double(r[i]);
+        }
+    if (!partials) return;
+    a = wave_sum(a);
+    b = wave_sum(b);
     if ((threadIdx.x & 63) == 0) {
         red[threadIdx.x >> 6][0] = a;
         red[threadIdx.x >> 6][1] = b;
@@ -390,7 +490,7 @@ __global__ __launch_bounds__(kThreads) void k_dot_rz_rr(int64_t N, const T *__re
     __syncthreads();
     if (threadIdx.x == 0) {
         double ta = 0.0, tb = 0.0;
-        for (int k = 0; k < kWavesPerBlock; ++k) {
+        for (int k = 0; k < kThreads / 64; ++k) {
             ta += red[k][0];
             tb += red[k][1];
         }
@@ -417,13 +517,16 @@ __global__ __launch_bounds__(kThreads) void k_zero_vec(int64_t n, T *__restrict_
     if (i < n) a[i] = T(0);
 }
 
+// One wavefront: totals of the G partials, then the solve's first scalars.
 __global__ void k_fin_init_amg(int G, const double *__restrict__ partials, KrylovScalars *sc, double rtol) {
-    if (threadIdx.x != 0) return;
     double a = 0.0, b = 0.0;
-    for (int k = 0; k < G; ++k) {
+    for (int k = threadIdx.x; k < G; k += 64) {
         a += partials[k];
         b += partials[G + k];
     }
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if (threadIdx.x != 0) return;
     sc->rho = a;
     sc->rho_pp[0] = a;
     sc->rho_pp[1] = a;
@@ -483,7 +586,7 @@ Cheb chebyshev_coeffs(double lmax, int degree) {
 template <typename T>
 struct AmgView {
     T *w, *rc, *d;             // fine temporaries
-    T *bc, *zc, *rcc, *dc, *wc;  // coarse temporaries
+    T *zc, *rcc, *dc, *dc2;    // coarse temporaries (two directions, used in turn)
     T *P, *cvals, *cdinv;
 };
 
@@ -497,11 +600,10 @@ AmgView<T> view(const fem_handle *h) {
     v.rc = f + N;
     v.d = f + 2 * N;
     T *c = static_cast<T *>(a.coarse_tmp);
-    v.bc = c;
-    v.zc = c + M;
-    v.rcc = c + 2 * M;
-    v.dc = c + 3 * M;
-    v.wc = c + 4 * M;
+    v.zc = c;
+    v.rcc = c + M;
+    v.dc = c + 2 * M;
+    v.dc2 = c + 3 * M;
     if constexpr (sizeof(T) == 4) v.P = a.P32;
     else v.P = a.P64;
     v.cvals = static_cast<T *>(a.cvals);
@@ -512,13 +614,32 @@ AmgView<T> view(const fem_handle *h) {
 template <typename T>
 void coarse_spmv(const fem_handle *h, const T *x, T *y, T alpha, const KrylovScalars *sc, hipStream_t s) {
     const Amg &a = *h->amg;
-    const unsigned G = grid_for(a.na * a.nc, kThreads);
+    const unsigned G = (grid_for(a.na, kWavesPerBlock) + 7) / 8 * 8;
     if (a.nc == 6)
-        hipLaunchKernelGGL((k_amg_cspmv<6, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol,
-                           static_cast<const T *>(a.cvals), x, y, alpha, sc);
+        hipLaunchKernelGGL((k_amg_rows<6, false, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol,
+                           static_cast<const T *>(a.cvals), x, y, alpha, nullptr, nullptr, nullptr, T(0), T(0), sc);
     else
-        hipLaunchKernelGGL((k_amg_cspmv<1, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol,
-                           static_cast<const T *>(a.cvals), x, y, alpha, sc);
+        hipLaunchKernelGGL((k_amg_rows<1, false, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol,
+                           static_cast<const T *>(a.cvals), x, y, alpha, nullptr, nullptr, nullptr, T(0), T(0), sc);
+    FEM_HIP(hipGetLastError());
+}
+
+// The Chebyshev steps after the first on the coarse operator (the first is in the
+// restriction), one kernel each; zc holds the result.
+template <typename T>
+void coarse_steps(const fem_handle *h, const AmgView<T> &v, const Cheb &c, const KrylovScalars *sc, hipStream_t s) {
+    const Amg &a = *h->amg;
+    const unsigned G = (grid_for(a.na, kWavesPerBlock) + 7) / 8 * 8;
+    T *d = v.dc, *dn = v.dc2;
+    for (size_t k = 0; k < c.c1.size(); ++k) {
+        if (a.nc == 6)
+            hipLaunchKernelGGL((k_amg_rows<6, true, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol, v.cvals,
+                               d, dn, T(1), v.rcc, v.zc, v.cdinv, T(c.c1[k]), T(c.c2[k]), sc);
+        else
+            hipLaunchKernelGGL((k_amg_rows<1, true, T>), dim3(G), dim3(kThreads), 0, s, a.na, a.cptr, a.ccol, v.cvals,
+                               d, dn, T(1), v.rcc, v.zc, v.cdinv, T(c.c1[k]), T(c.c2[k]), sc);
+        std::swap(d, dn);
+    }
     FEM_HIP(hipGetLastError());
 }
 
@@ -736,7 +857,7 @@ void amg_setup(fem_handle *h) {
     a->cvals = dev_alloc(h, size_t(nbc) * nc * nc * sizeof(double));
     a->cdinv = dev_alloc(h, size_t(na) * nc * sizeof(double));
     a->fine_tmp = dev_alloc(h, 3 * size_t(N) * sizeof(double));
-    a->coarse_tmp = dev_alloc(h, 5 * size_t(na) * nc * sizeof(double));
+    a->coarse_tmp = dev_alloc(h, 4 * size_t(na) * nc * sizeof(double));
     a->red = static_cast<double *>(dev_alloc(h, 2 * kRedGrid * sizeof(double)));
     FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&a->host_red), 2 * kRedGrid * sizeof(double)));
     h->amg = a;
@@ -799,30 +920,29 @@ void amg_refresh(fem_handle *h, const T *values, const T *dinv, int precision, i
     a.cdeg = coarse_degree;
 }
 
-// z = M r (one V-cycle).
+// z = M r (one V-cycle).  presmoothed: z already holds the first (and only) pre-smoothing
+// step.  partials: also the partial sums of (r, z) and (r, r), one per block of Gd.
 template <typename T>
 static void vcycle(fem_handle *h, const T *values, const T *dinv, const T *r, T *z, int sdeg, int cdeg,
-                   const KrylovScalars *sc, hipStream_t s) {
+                   const KrylovScalars *sc, hipStream_t s, bool presmoothed = false, double *partials = nullptr,
+                   int Gd = 0) {
     Amg &a = *h->amg;
     const Graph &g = h->g;
     AmgView<T> v = view<T>(h);
     const Cheb cf = chebyshev_coeffs(a.lmax, sdeg), cc = chebyshev_coeffs(a.lmax_c, cdeg);
     auto fine_op = [&](const T *x, T *y) { launch_spmv_sc<T>(h, values, x, y, T(1), T(0), sc, s); };
-    auto coarse_op = [&](const T *x, T *y) { coarse_spmv<T>(h, x, y, T(1), sc, s); };
-    const int64_t M = a.na * a.nc;
     // pre-smoothing from 0
-    chebyshev_run<T>(g.N, cf, fine_op, r, dinv, z, v.w, v.rc, v.d, 0, sc, s);
-    // restriction of r - A z
+    if (!presmoothed) chebyshev_run<T>(g.N, cf, fine_op, r, dinv, z, v.w, v.rc, v.d, 0, sc, s);
+    // restriction of r - A z with the first coarse step, the other steps, prolongation
     fine_op(z, v.w);
     const unsigned Ga = grid_for(a.na, kWavesPerBlock);
     if (a.nc == 6)
         hipLaunchKernelGGL((k_amg_restrict<3, 6, T>), dim3(Ga), dim3(kThreads), 0, s, a.na, a.agg_ptr, a.agg_nodes,
-                           v.P, r, v.w, v.bc, sc);
+                           v.P, r, v.w, v.cdinv, T(cc.inv_theta), v.rcc, v.dc, v.zc, sc);
     else
         hipLaunchKernelGGL((k_amg_restrict<1, 1, T>), dim3(Ga), dim3(kThreads), 0, s, a.na, a.agg_ptr, a.agg_nodes,
-                           v.P, r, v.w, v.bc, sc);
-    // coarse correction
-    chebyshev_run<T>(M, cc, coarse_op, v.bc, v.cdinv, v.zc, v.wc, v.rcc, v.dc, 0, sc, s);
+                           v.P, r, v.w, v.cdinv, T(cc.inv_theta), v.rcc, v.dc, v.zc, sc);
+    coarse_steps<T>(h, v, cc, sc, s);
     if (a.nc == 6)
         hipLaunchKernelGGL((k_amg_prolong<3, 6, T>), dim3(grid_for(g.Nn, kThreads)), dim3(kThreads), 0, s, g.Nn,
                            a.agg, v.P, v.zc, z, sc);
@@ -830,9 +950,14 @@ static void vcycle(fem_handle *h, const T *values, const T *dinv, const T *r, T 
         hipLaunchKernelGGL((k_amg_prolong<1, 1, T>), dim3(grid_for(g.Nn, kThreads)), dim3(kThreads), 0, s, g.Nn,
                            a.agg, v.P, v.zc, z, sc);
     FEM_HIP(hipGetLastError());
-    // post-smoothing continued from z
+    // post-smoothing continued from z (a single step goes with the inner products)
     fine_op(z, v.w);
-    chebyshev_run<T>(g.N, cf, fine_op, r, dinv, z, v.w, v.rc, v.d, 1, sc, s);
+    const bool last = sdeg == 1;
+    if (!last) chebyshev_run<T>(g.N, cf, fine_op, r, dinv, z, v.w, v.rc, v.d, 1, sc, s);
+    if (last || partials)
+        hipLaunchKernelGGL((k_dot_rz_rr<T>), dim3(partials ? Gd : krylov_vec_grid_of(h)), dim3(kThreads), 0, s, g.N, r,
+                           z, last ? v.w : nullptr, dinv, T(cf.inv_theta), partials, sc);
+    FEM_HIP(hipGetLastError());
 }
 
 template <typename T>
@@ -847,10 +972,9 @@ void kry_cg_amg_init(fem_handle *h, const KrylovVecs<T> &k, const T *b, double r
     const unsigned G = grid_for(N, kThreads);
     hipLaunchKernelGGL((k_copy_vec<T>), dim3(G), dim3(kThreads), 0, s, N, b, k.r);
     hipLaunchKernelGGL((k_zero_vec<T>), dim3(G), dim3(kThreads), 0, s, N, k.x);
-    vcycle<T>(h, k.A, k.dinv, k.r, k.rh, h->amg->sdeg, h->amg->cdeg, nullptr, s);
+    const int Gd = krylov_vec_grid_of(h);
+    vcycle<T>(h, k.A, k.dinv, k.r, k.rh, h->amg->sdeg, h->amg->cdeg, nullptr, s, false, k.partials, Gd);
     hipLaunchKernelGGL((k_copy_vec<T>), dim3(G), dim3(kThreads), 0, s, N, k.rh, k.p);
-    const int Gd = krylov_grid(h);
-    hipLaunchKernelGGL((k_dot_rz_rr<T>), dim3(Gd), dim3(kThreads), 0, s, N, k.r, k.rh, k.partials, nullptr);
     hipLaunchKernelGGL(k_fin_init_amg, dim3(1), dim3(64), 0, s, Gd, k.partials, k.sc, rtol);
     FEM_HIP(hipGetLastError());
 }
@@ -862,10 +986,11 @@ void kry_cg_amg_iter(fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_t 
     const int G = kry_spmv_q<T>(h, k, s);  // q = K p, (p, q) partials
     if (ev) FEM_HIP(hipEventRecord(ev[1], s));
     const int Gv = krylov_vec_grid_of(h);
+    const bool one = h->amg->sdeg == 1;  // a single smoothing step: fused with its neighbours
     hipLaunchKernelGGL((k_cg_xr_plain<T>), dim3(Gv), dim3(kThreads), 0, s, N, k.x, k.r, k.p, k.v, k.partials, G,
-                       k.sc, it);
-    vcycle<T>(h, k.A, k.dinv, k.r, k.rh, h->amg->sdeg, h->amg->cdeg, k.sc, s);
-    hipLaunchKernelGGL((k_dot_rz_rr<T>), dim3(Gv), dim3(kThreads), 0, s, N, k.r, k.rh, k.partials2, k.sc);
+                       k.sc, it, one ? k.rh : nullptr, k.dinv,
+                       T(chebyshev_coeffs(h->amg->lmax, h->amg->sdeg).inv_theta));
+    vcycle<T>(h, k.A, k.dinv, k.r, k.rh, h->amg->sdeg, h->amg->cdeg, k.sc, s, one, k.partials2, Gv);
     FEM_HIP(hipGetLastError());
     kry_cg_p_update<T>(h, k, it, s);
 }

@@ -354,15 +354,6 @@ __device__ __forceinline__ void load_node(const double *coords, const int32_t *c
     for (int i = 0; i < ND; ++i) U[i] = T((m[i] ? 0.0 : v[i]) - (m0[i] ? 0.0 : v0[i]));
 }
 
-// Hand-off of LDS data between lanes of one wavefront: a wavefront's LDS operations are
-// performed in program order, so a lane reads what other lanes of its wavefront wrote
-// before this point; the fence (wavefront scope) and the wave barrier keep the compiler
-// from moving LDS accesses across it.  Neither emits an instruction.
-__device__ __forceinline__ void wave_lds_handoff() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // ------------------------------------------------------------------ residual-type kernels
 enum { VEC_RESIDUAL = 0, VEC_JVP = 1, VEC_VJP = 2, VEC_LIFT = 3, VEC_MASS = 4 };
 

@@ -34,6 +34,25 @@ __device__ __forceinline__ double dpp_read(double v) {
     return __builtin_bit_cast(double, (static_cast<unsigned long long>(unsigned(hi)) << 32) | unsigned(lo));
 }
 
+// 16-byte vector view of an FP32 (4 lanes) or FP64 (2 lanes) array.
+template <typename T>
+struct Vec16 {
+    static constexpr int W = 16 / int(sizeof(T));
+    typedef T type __attribute__((ext_vector_type(W)));
+    __device__ static type ld(const T *a, int64_t i) { return reinterpret_cast<const type *>(a)[i]; }
+    __device__ static void st(T *a, int64_t i, type v) { reinterpret_cast<type *>(a)[i] = v; }
+    __device__ static void st_nt(T *a, int64_t i, type v) { __builtin_nontemporal_store(v, reinterpret_cast<type *>(a) + i); }
+};
+
+// Hand-off of LDS data between lanes of one wavefront: a wavefront's LDS operations are
+// performed in program order, so a lane reads what other lanes of its wavefront wrote
+// before this point; the fence (wavefront scope) and the wave barrier keep the compiler
+// from moving LDS accesses across it.  Neither emits an instruction.
+__device__ __forceinline__ void wave_lds_handoff() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Sum over the aligned group of 8 lanes (all 8 lanes receive it).
 template <typename T>
 __device__ __forceinline__ T lane_sum8(T v) {

@@ -696,16 +696,6 @@ __global__ __launch_bounds__(kThreads) void k_fin_bicg_xr(int G, const double *_
     }
 }
 
-// 16-byte vector view of an FP32 (4 lanes) or FP64 (2 lanes) array.
-template <typename T>
-struct Vec16 {
-    static constexpr int W = 16 / int(sizeof(T));
-    typedef T type __attribute__((ext_vector_type(W)));
-    __device__ static type ld(const T *a, int64_t i) { return reinterpret_cast<const type *>(a)[i]; }
-    __device__ static void st(T *a, int64_t i, type v) { reinterpret_cast<type *>(a)[i] = v; }
-    __device__ static void st_nt(T *a, int64_t i, type v) { __builtin_nontemporal_store(v, reinterpret_cast<type *>(a) + i); }
-};
-
 // CG with the scalar updates folded into the vector kernels.  Each block sums the
 // previous kernel's per-block partials itself (same order in every block, so all
 // blocks agree bit for bit), which removes the one-block finalize launches.
