@@ -1,7 +1,6 @@
 // C ABI of libfem: argument checks, handle lifetime, error translation.
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 #include <cstring>
 #include <new>
 
@@ -169,11 +168,6 @@ int fem_build_pattern(const fem_mesh_desc *d, fem_handle **out, int64_t *n_dofs,
         if (N) FEM_HIP(hipMemcpy(h->m.mask, h->m.host_mask.data(), N, hipMemcpyHostToDevice));
         fem::build_load_vector(h, d);
         fem::build_graph(h, d);
-        // SpMV group width: a power of two covering the typical node degree; FEM_SPMV_GROUP overrides it.
-        if (const char *gs = std::getenv("FEM_SPMV_GROUP")) {
-            int gv = std::atoi(gs);
-            if (gv == 4 || gv == 8 || gv == 16 || gv == 32) h->spmv_group = gv;
-        }
         h->status = static_cast<int *>(fem::dev_alloc(h, sizeof(int)));
         FEM_HIP(hipMemset(h->status, 0, sizeof(int)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_status), sizeof(int)));

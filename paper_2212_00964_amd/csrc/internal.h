@@ -159,7 +159,6 @@ struct fem_handle {
     double *host_scalar = nullptr;
     fem::KrylovScalars *host_kry = nullptr;
     std::vector<hipEvent_t> events;           // SpMV timing events (profile_spmv)
-    int spmv_group = 16;                      // SpMV tuning knob (nodes in flight per lane group)
     int num_cus = 256;                        // compute units of the device
     std::vector<void *> allocations;          // device allocations owned by the handle
     fem::Filter filter;                       // fem_filter_setup (owns its allocations)

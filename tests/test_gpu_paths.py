@@ -63,3 +63,26 @@ def test_tangent_at_tile_edges(law, n):
         y_ref = prob.spmv(K, torch.as_tensor(x, device=DEV))
         assert_parity(host(y), host(y_ref), 1e-13, f"{law} {shape} symmetric blocks")
         prob.close()
+
+
+# nodes around the eight of a block of the transposed product, and around the 32 lanes of a
+# group (the fan's axis nodes have more neighbours).  Tolerances as in test_gpu_parity.py's
+# products: FP64 1e-13, FP32 5e-6.
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-13), (torch.float32, 5e-6)])
+@pytest.mark.parametrize("kind", ["poisson", "linear", "nh", "fan"])
+@pytest.mark.parametrize("n", [1, 2, 3, 7])
+def test_transposed_product_at_tile_edges(kind, n, dtype, tol):
+    p = gen.nh_fan(3 + 2 * n, n) if kind == "fan" else _line(kind, n)
+    u = 0.002 * np.random.default_rng(n).standard_normal(p.n_dofs)
+    pat = orc.Pattern(p)
+    _, K_ref = orc.assemble(p, pat, u)
+    prob = fem.Problem(p, DEV)
+    _, K = prob.assemble(u, residual=False, values_dtype=dtype)
+    x = np.random.default_rng(n + 1).standard_normal(p.n_dofs)
+    y0 = np.random.default_rng(n + 2).standard_normal(p.n_dofs)
+    for alpha, beta in ((1.0, 0.0), (-0.6, 1.7)):
+        y = torch.as_tensor(y0 if beta else np.full(p.n_dofs, np.nan), dtype=dtype, device=DEV)
+        prob.spmv(K, torch.as_tensor(x, dtype=dtype, device=DEV), transpose=True, alpha=alpha, beta=beta, y=y)
+        expect = alpha * (pat.matrix(K_ref).T @ x) + (beta * y0 if beta else 0.0)
+        assert_parity(host(y), expect, tol, f"{kind} {n}")
+    prob.close()
