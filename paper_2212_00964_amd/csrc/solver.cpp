@@ -168,36 +168,44 @@ int krylov_solve(fem_handle *h, SolveWork &w, const T *A, const fem_solve_opts &
     const bool cg = o.krylov == FEM_KRYLOV_CG;
     const bool amg = o.precond == FEM_PRECOND_AMG;  // CG only (checked at the ABI)
     const T *b = static_cast<const T *>(w.b);
-    if (amg) kry_cg_amg_init<T>(h, k, b, rtol, s);
-    else if (cg) kry_cg_init<T>(h, k, b, rtol, s);
-    else kry_bicg_init<T>(h, k, b, rtol, s);
     // a two-level iteration costs several SpMVs: read convergence back more often
     const int every = amg ? std::max(1, std::min(o.check_every, 4)) : std::max(1, o.check_every);
+    const bool prof = o.profile_spmv != 0;
+    KrylovScalars hs{};
+    // small systems: the whole solve in one kernel (the limit as in the loop below, which
+    // ends after a whole number of check intervals)
+    const int64_t limit = (std::max<int64_t>(o.krylov_max_it, 1) + every - 1) / every * every;
+    const bool resident = cg && !amg && !prof && kry_cg_resident<T>(h, k, b, rtol, limit, hs, s);
+    if (!resident) {
+        if (amg) kry_cg_amg_init<T>(h, k, b, rtol, s);
+        else if (cg) kry_cg_init<T>(h, k, b, rtol, s);
+        else kry_bicg_init<T>(h, k, b, rtol, s);
+    }
     const int spmv_per_it = cg ? 1 : 2;
     std::vector<hipEvent_t> &ev = h->events;
-    const bool prof = o.profile_spmv != 0;
     if (prof && ev.size() < 4) {
         size_t old = ev.size();
         ev.resize(4);
         for (size_t i = old; i < ev.size(); ++i) FEM_HIP(hipEventCreate(&ev[i]));
     }
     int its_done = 0;
-    KrylovScalars hs{};
     for (int it = 0;; it += every) {
-        for (int j = 0; j < every; ++j) {
-            // timing samples the middle iteration of each check interval (away from the
-            // host read-back at its end): an event pair around every SpMV would itself
-            // cost about 4% of the iteration time
-            hipEvent_t *e = (prof && j == every / 2) ? &ev[0] : nullptr;
-            if (amg) kry_cg_amg_iter<T>(h, k, it + j, s, e);
-            else if (cg) kry_cg_iter<T>(h, k, it + j, s, e);
-            else kry_bicg_iter<T>(h, k, it + j, s, e);
+        if (!resident) {
+            for (int j = 0; j < every; ++j) {
+                // timing samples the middle iteration of each check interval (away from the
+                // host read-back at its end): an event pair around every SpMV would itself
+                // cost about 4% of the iteration time
+                hipEvent_t *e = (prof && j == every / 2) ? &ev[0] : nullptr;
+                if (amg) kry_cg_amg_iter<T>(h, k, it + j, s, e);
+                else if (cg) kry_cg_iter<T>(h, k, it + j, s, e);
+                else kry_bicg_iter<T>(h, k, it + j, s, e);
+            }
+            if (!cg) kry_bicg_check<T>(h, k, it + every, s);
+            else if (!amg) kry_cg_check<T>(h, k, it + every, s);
+            FEM_HIP(hipMemcpyAsync(h->host_kry, w.sc, kScalarsHostBytes, hipMemcpyDeviceToHost, s));
+            FEM_HIP(hipStreamSynchronize(s));
+            std::memcpy(&hs, h->host_kry, kScalarsHostBytes);
         }
-        if (!cg) kry_bicg_check<T>(h, k, it + every, s);
-        else if (!amg) kry_cg_check<T>(h, k, it + every, s);
-        FEM_HIP(hipMemcpyAsync(h->host_kry, w.sc, kScalarsHostBytes, hipMemcpyDeviceToHost, s));
-        FEM_HIP(hipStreamSynchronize(s));
-        std::memcpy(&hs, h->host_kry, kScalarsHostBytes);
         if (prof && st && hs.its > its_done + every / 2) {  // the sampled iteration did an update
             for (int q = 0; q < spmv_per_it; ++q) {
                 float ms = 0.f;
@@ -218,7 +226,7 @@ int krylov_solve(fem_handle *h, SolveWork &w, const T *A, const fem_solve_opts &
             if (hs.its == 0) throw Error(FEM_EBREAKDOWN, "Krylov breakdown before the first update");
             break;  // keep the last iterate; the outer loop measures its true residual
         }
-        if (it + every >= o.krylov_max_it) break;
+        if (resident || it + every >= o.krylov_max_it) break;
     }
     if (k.fold) launch_mul_inplace<T>(k.x, k.dinv, h->g.N, s);  // x = D^{-1} y
     const double relres = hs.bnorm2 > 0.0 ? std::sqrt(hs.rnorm2 / hs.bnorm2) : 0.0;

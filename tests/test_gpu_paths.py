@@ -86,3 +86,79 @@ def test_transposed_product_at_tile_edges(kind, n, dtype, tol):
         expect = alpha * (pat.matrix(K_ref).T @ x) + (beta * y0 if beta else 0.0)
         assert_parity(host(y), expect, tol, f"{kind} {n}")
     prob.close()
+
+
+# CG on small systems runs in one kernel: nodes around the 64 a workgroup takes at a time,
+# several passes of it, several workgroups and their exchange through the first one
+# (n x 7 x 7 elements: 64 (n + 1) nodes).  Oracle tolerance as in test_gpu_parity.py's solves.
+@pytest.mark.parametrize("precond", [0, 1])
+@pytest.mark.parametrize("law,shape", [("poisson", (1, 1, 1)), ("poisson", (15, 1, 1)), ("poisson", (20, 1, 1)),
+                                       ("poisson", (17, 7, 7)), ("linear", (1, 1, 1)), ("linear", (15, 1, 1)),
+                                       ("linear", (16, 1, 1)), ("linear", (16, 7, 7)), ("linear", (5, 4, 3))])
+def test_resident_cg(law, shape, precond):
+    p = _line(law, *shape)
+    u_ref = orc.newton_solve(p, linear="direct", rtol=1e-13)
+    prob = fem.Problem(p, DEV)
+    for precision, newton, krylov, tol in ((fem.PREC_FP64, 1e-11, 1e-8, 1e-10), (fem.PREC_MIXED, 1e-10, 1e-5, 1e-6),
+                                           (fem.PREC_MIXED_V64, 1e-10, 1e-5, 1e-6)):
+        u, st = prob.newton_solve(krylov=fem.CG, precond=precond, precision=precision, krylov_rtol=krylov,
+                                  newton_rtol=newton)
+        assert st.krylov_unconverged == 0
+        assert_parity(host(u), u_ref, tol, f"{law} {shape} precision {precision}")
+    prob.close()
+
+
+def test_resident_cg_over_several_launches():
+    """A slender beam whose solve outlasts one launch (1,024 iterations): Newton's own
+    residual after the one correction has to come down to what CG was asked for."""
+    p = gen.cantilever(96, 1, 1, L=(96.0, 1.0, 1.0))
+    prob = fem.Problem(p, DEV)
+    for max_it in (20000, 1040):
+        u, st = prob.newton_solve(krylov=fem.CG, krylov_rtol=1e-6, newton_rtol=1e-5, krylov_max_it=max_it)
+        assert st.krylov_its[0] > 1024 if max_it == 20000 else st.krylov_its[0] <= 1040, st.as_dict()
+        if max_it == 20000:
+            assert st.n_hist <= 3, st.as_dict()
+    prob.close()
+
+
+def test_resident_cg_in_concurrent_threads():
+    """Solves of two handles at once, on streams of their own, give what they give alone."""
+    import threading
+
+    probs = [fem.Problem(gen.cantilever(20, 16, 16, E=70e3 * (1 + i)), DEV) for i in range(2)]
+    opts = dict(krylov=fem.CG, krylov_rtol=1e-8, newton_rtol=1e-7)
+    alone = [host(q.newton_solve(**opts)[0]).copy() for q in probs]
+    out = [None, None]
+
+    def work(i):
+        torch.cuda.set_device(0)
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(4):
+                u, _ = probs[i].newton_solve(**opts)
+            st.synchronize()
+        out[i] = u.cpu().numpy()
+
+    ths = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for th in ths:
+        th.start()
+    for th in ths:
+        th.join()
+    for i in range(2):
+        assert np.array_equal(out[i], alone[i])
+    for q in probs:
+        q.close()
+
+
+@pytest.mark.parametrize("shape", [(30, 26, 24), (36, 24, 24)])
+def test_resident_cg_against_separate_kernels(shape):
+    """About 170 workgroups, whose sums go through the first one (timing the products takes
+    the separate kernels).  Both leave |r| <= 1e-11 |b|; 300 iterations for ten digits put
+    the condition number of the scaled matrix at 600, so 2 x 600 x 1e-11 apart at most."""
+    prob = fem.Problem(gen.cantilever(*shape), DEV)
+    opts = dict(krylov=fem.CG, krylov_rtol=1e-9, newton_rtol=1e-11)
+    u, st = prob.newton_solve(**opts)
+    u_sep, st_sep = prob.newton_solve(profile_spmv=1, **opts)
+    assert st.spmv_calls == 0 and st_sep.spmv_calls > 0
+    assert_parity(host(u), host(u_sep), 1.2e-8)
+    prob.close()
