@@ -172,8 +172,8 @@ int fem_build_pattern(const fem_mesh_desc *d, fem_handle **out, int64_t *n_dofs,
         fem::build_graph(h, d);
         h->status = static_cast<int *>(fem::dev_alloc(h, sizeof(int)));
         FEM_HIP(hipMemset(h->status, 0, sizeof(int)));
-        h->cg_slots = static_cast<unsigned long long *>(fem::dev_alloc(h, fem::resident_slots_bytes(h)));
-        FEM_HIP(hipMemset(h->cg_slots, 0, fem::resident_slots_bytes(h)));
+        h->res_slots = static_cast<unsigned long long *>(fem::dev_alloc(h, fem::resident_slots_bytes(h)));
+        FEM_HIP(hipMemset(h->res_slots, 0, fem::resident_slots_bytes(h)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_status), sizeof(int)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_scalar), sizeof(double)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_kry), fem::kScalarsHostBytes));

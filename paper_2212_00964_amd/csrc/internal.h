@@ -64,7 +64,7 @@ struct KrylovScalars {
     // |rhat|^2 and the smallest |r|^2 so far -- written by one kernel of iteration k and
     // read by kernels of iteration k + 1, never by blocks of the kernel writing them
     double alpha_pp[2], omega_pp[2], rh2_pp[2], rmin2_pp[2];
-    int aborted;  // resident CG: first round number of a launch that gave up waiting
+    int aborted;  // one-kernel solves, in the host's copy: why a launch left the solve undone
 };
 constexpr size_t kScalarsHostBytes = sizeof(KrylovScalars);
 
@@ -163,9 +163,10 @@ struct fem_handle {
     int num_cus = 256;                        // compute units of the device
     int lds_bytes = 65536;                    // LDS of a workgroup
     int clock_khz = 100000;                   // rate of the device's wall clock
-    unsigned long long *cg_slots = nullptr;   // exchange slots of the resident CG (cg_resident.hip)
-    unsigned cg_epoch = 0;                    // last round number it used
-    bool cg_slots_off = false;                // its workgroups could not run together
+    unsigned long long *res_slots = nullptr;  // exchange lines of the one-kernel solves (krylov_resident.hip)
+    unsigned res_epoch = 0;                   // last round number they used
+    bool res_off = false;                     // their workgroups could not run together
+    bool res_misfit[2][2][2] = {};            // [CG][FP64 vectors][FP64 values]: too many touched nodes
     std::vector<void *> allocations;          // device allocations owned by the handle
     fem::Filter filter;                       // fem_filter_setup (owns its allocations)
     double *red_partials = nullptr;           // [kRedGrid] reduction partials (fem_element_volumes, fem_set_load)
@@ -262,12 +263,13 @@ void kry_cg_init(const fem_handle *h, const KrylovVecs<T> &k, const T *b, double
 // Likewise for CG when its SpMV forms the next direction (nothing to do otherwise).
 template <typename T>
 void kry_cg_check(const fem_handle *h, const KrylovVecs<T> &k, int it, hipStream_t s);
-// CG in one kernel where the matrix fits the registers (cg_resident.hip): K x = b from
-// x = 0 to rtol, at most max_its iterations; fills hs.  False: not done, x is undefined
-// (the system does not fit, or its workgroups could not run together).
+// A whole CG or (with the folded point Jacobi) BiCGSTAB solve in one kernel, for systems up
+// to about twice what the registers hold (krylov_resident.hip): K x = b from x = 0 to rtol, at most
+// max_its iterations; fills hs.  False: not done, x is undefined (the system does not
+// fit, or its workgroups could not run together).
 template <typename T>
-bool kry_cg_resident(fem_handle *h, const KrylovVecs<T> &k, const T *b, double rtol, int64_t max_its,
-                     KrylovScalars &hs, hipStream_t s);
+bool kry_resident(fem_handle *h, const KrylovVecs<T> &k, bool cg, const T *b, double rtol, int64_t max_its,
+                  KrylovScalars &hs, hipStream_t s);
 size_t resident_slots_bytes(const fem_handle *h);
 // Two-level preconditioned CG (amg.hip): init (z = M b) and iteration `it`.
 template <typename T>

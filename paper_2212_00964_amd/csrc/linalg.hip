@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "bicg_rules.h"
 #include "internal.h"
 #include "lanes.h"
 
@@ -174,48 +175,11 @@ __device__ bool cg_p_scalars(const double *partials, int count, KrylovScalars *s
     return !(nan || conv);
 }
 
-// Finite-precision safeguards of the fused BiCGSTAB, for FP32 vectors.  Omega limit:
-// when t and s are nearly orthogonal (|(t, s)| < Omega |t| |s|), omega = (t, s) / (t, t)
-// is scaled up by Omega / cos(t, s), which keeps the BiCG coefficients of the next
-// steps accurate (Sleijpen and van der Vorst's 'limited omega', Omega = 0.7).  Restart
-// floor: see bicg_rho_floor.  Measured on the 5-step 100^3 and 200x100x100 neo-Hookean
-// solves: FP32 sweeps without the floor diverged on the larger one; the limit cut its
-// FP32 iterations by a third (27,704 against 41,951) but cost the FP64 vectors 48% more
-// (23,236 against 15,705), so FP64 runs plain BiCGSTAB.
-constexpr double kOmegaLimitF32 = 0.7;
-constexpr double kRhoFloorF32 = 1e-5;
-
-template <typename T>
-__device__ __forceinline__ double bicg_omega_limit() { return sizeof(T) == 4 ? kOmegaLimitF32 : 0.0; }
-
-struct BicgStart {
-    double rho, r2, rh2, rmin2;
-    bool nan, conv, div, restart;
-};
-
-// Restart floor of |(rhat, r)| / (|rhat| |r|): below it the shadow inner product has
-// lost its meaning.  In FP32 the vectors carry relative errors near 1e-7 that grow over
-// long solves, so the floor sits well above that noise; FP64 keeps the classic 1e-9.
-template <typename T>
-__device__ __forceinline__ double bicg_rho_floor() { return sizeof(T) == 4 ? kRhoFloorF32 : 1e-9; }
-
-// Tests at the start of iteration i (>= 1) from the partial sums tot = ((rhat, r), |r|^2)
-// of iteration i - 1: the same rules as the unfused finalize.
-__device__ BicgStart bicg_start(const double tot[2], const KrylovScalars *sc, int i, double rho_floor) {
+// Tests at the start of iteration i (>= 1), with the scalars of iteration i - 1.
+__device__ __forceinline__ BicgStart bicg_start_at(const double tot[2], const KrylovScalars *sc, int i,
+                                                   double rho_floor) {
     const int q = (i - 1) & 1;
-    BicgStart b;
-    b.r2 = tot[1];
-    b.nan = !isfinite(tot[0]) || !isfinite(tot[1]);
-    b.conv = !b.nan && tot[1] <= sc->tol2;
-    b.div = !b.nan && !b.conv && tot[1] > 1e12 * sc->bnorm2;
-    const double rh2 = sc->rh2_pp[q], rmin2 = sc->rmin2_pp[q];
-    // (rhat, r) lost its size relative to |rhat||r|, omega vanished, or the residual
-    // grew 1000x above its best value: restart from the current r
-    b.restart = !(fabs(tot[0]) > rho_floor * sqrt(rh2 * tot[1])) || sc->omega_pp[q] == 0.0 || tot[1] > 1e6 * rmin2;
-    b.rho = b.restart ? tot[1] : tot[0];
-    b.rh2 = b.restart ? tot[1] : rh2;
-    b.rmin2 = fmin(rmin2, tot[1]);
-    return b;
+    return bicg_start(tot, sc->tol2, sc->bnorm2, sc->rh2_pp[q], sc->rmin2_pp[q], sc->omega_pp[q], rho_floor);
 }
 
 __device__ __forceinline__ void bicg_publish_start(const BicgStart &b, KrylovScalars *sc, int i) {
@@ -235,7 +199,7 @@ __device__ bool bicg_p_scalars(const double *partials, int count, KrylovScalars 
     if (it == 0) return true;
     double tot[2];
     sum_partials<2>(partials, count, tot);
-    const BicgStart b = bicg_start(tot, sc, it, bicg_rho_floor<T>());
+    const BicgStart b = bicg_start_at(tot, sc, it, bicg_rho_floor<T>());
     const int q = (it - 1) & 1;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         bicg_publish_start(b, sc, it);
@@ -893,12 +857,7 @@ __global__ __launch_bounds__(kThreads) void k_bicg_xr_fused(int64_t N, int it, T
     if (stopped(sc)) return;
     double tot[3];  // (t, s), (t, t), (s, s)
     sum_partials<3>(sp_partials, sp_count, tot);
-    double omega = (tot[1] > 0.0 && isfinite(tot[1])) ? tot[0] / tot[1] : 0.0;
-    const double om_lim = bicg_omega_limit<T>();
-    if (om_lim > 0.0 && omega != 0.0 && tot[2] > 0.0) {
-        const double c = fabs(tot[0]) / sqrt(tot[1] * tot[2]);
-        if (c < om_lim) omega *= om_lim / c;
-    }
+    const double omega = bicg_omega<T>(tot);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc->omega_pp[it & 1] = omega;
         sc->omega = omega;
@@ -937,7 +896,7 @@ __global__ __launch_bounds__(kThreads) void k_bicg_check(int it, const double *_
     if (stopped(sc) || it == 0) return;
     double tot[2];
     sum_partials<2>(xr_partials, xr_count, tot);
-    const BicgStart b = bicg_start(tot, sc, it, rho_floor);
+    const BicgStart b = bicg_start_at(tot, sc, it, rho_floor);
     if (threadIdx.x == 0) bicg_publish_start(b, sc, it);
 }
 

@@ -172,10 +172,10 @@ int krylov_solve(fem_handle *h, SolveWork &w, const T *A, const fem_solve_opts &
     const int every = amg ? std::max(1, std::min(o.check_every, 4)) : std::max(1, o.check_every);
     const bool prof = o.profile_spmv != 0;
     KrylovScalars hs{};
-    // small systems: the whole solve in one kernel (the limit as in the loop below, which
+    // systems that fit: the whole solve in one kernel (the limit as in the loop below, which
     // ends after a whole number of check intervals)
     const int64_t limit = (std::max<int64_t>(o.krylov_max_it, 1) + every - 1) / every * every;
-    const bool resident = cg && !amg && !prof && kry_cg_resident<T>(h, k, b, rtol, limit, hs, s);
+    const bool resident = !amg && !prof && kry_resident<T>(h, k, cg, b, rtol, limit, hs, s);
     if (!resident) {
         if (amg) kry_cg_amg_init<T>(h, k, b, rtol, s);
         else if (cg) kry_cg_init<T>(h, k, b, rtol, s);

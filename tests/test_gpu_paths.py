@@ -162,3 +162,38 @@ def test_resident_cg_against_separate_kernels(shape):
     assert st.spmv_calls == 0 and st_sep.spmv_calls > 0
     assert_parity(host(u), host(u_sep), 1.2e-8)
     prob.close()
+
+
+# BiCGSTAB in one kernel at the same edges; tolerances as in test_gpu_parity.py's solves.
+@pytest.mark.parametrize("law,shape", [("poisson", (15, 1, 1)), ("poisson", (17, 7, 7)), ("linear", (1, 1, 1)),
+                                       ("linear", (15, 1, 1)), ("linear", (16, 1, 1)), ("nh", (5, 4, 3)),
+                                       ("nh", (16, 7, 7))])
+def test_resident_bicgstab(law, shape):
+    p = _line(law, *shape)
+    u_ref = orc.newton_solve(p, linear="direct", rtol=1e-13)
+    prob = fem.Problem(p, DEV)
+    for precision, newton, krylov, tol in ((fem.PREC_FP64, 1e-11, 1e-8, 1e-10), (fem.PREC_MIXED, 1e-10, 1e-5, 1e-6),
+                                           (fem.PREC_MIXED_V64, 1e-10, 1e-5, 1e-6)):
+        u, st = prob.newton_solve(krylov=fem.BICGSTAB, precision=precision, krylov_rtol=krylov, newton_rtol=newton)
+        assert_parity(host(u), u_ref, tol, f"{law} {shape} precision {precision}")
+    prob.close()
+
+
+@pytest.mark.parametrize("relabel", [False, True])
+@pytest.mark.parametrize("krylov", [0, 1])
+@pytest.mark.parametrize("law,shape,precision", [("linear", (40, 30, 27), 0), ("linear", (42, 41, 40), 1),
+                                                 ("linear", (42, 41, 40), 2), ("poisson", (44, 41, 40), 0)])
+def test_resident_rows_beyond_registers(law, shape, precision, krylov, relabel):
+    """Meshes with more nodes per workgroup than the registers hold (128 with FP64, 256 with
+    FP32 values or one dof) against the separate kernels; with random node numbers some
+    do not fit the LDS and take those too.  Both leave |r| <= 1e-9 |b|, and the condition
+    number of the scaled matrix is below 2,000 on these meshes: 2 x 2,000 x 1e-9 apart."""
+    p = _line(law, *shape)
+    if relabel:
+        p = gen.relabel(p, 7)[0]
+    prob = fem.Problem(p, DEV)
+    opts = dict(krylov=krylov, precision=precision, krylov_rtol=1e-6, newton_rtol=1e-9)
+    u, _ = prob.newton_solve(**opts)
+    u_sep, _ = prob.newton_solve(profile_spmv=1, **opts)
+    assert_parity(host(u), host(u_sep), 4e-6)
+    prob.close()
