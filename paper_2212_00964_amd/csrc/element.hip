@@ -632,28 +632,41 @@ __global__ __launch_bounds__(kThreads) void k_j2_average(int64_t Ne, const doubl
     }
 }
 
-// Sum element contributions per dof.
+// Sum element contributions per dof, eight lanes per node, one of its slots each: the slots of
+// consecutive nodes are one run of memory, read once.  What bounds it is that run: 64^3
+// elements, 60 MB, 18.8 -> 11.7 us; 100^3, 240 MB, 73 -> 53 us (a thread per dof walked its
+// node's slots at a stride).
 // VEC_RESIDUAL: out[d] = sum - lf * F[d], 0 on Dirichlet dofs.
 // VEC_JVP:      out[d] = sum, v[d] on Dirichlet dofs.
 // VEC_LIFT:     out[d] = sum, 0 on Dirichlet dofs.
 template <int ND, int MODE>
-__global__ __launch_bounds__(256) void k_gather_vec(int64_t N, const int64_t *__restrict__ ne_ptr,
+__global__ __launch_bounds__(256) void k_gather_vec(int64_t Nn, const int64_t *__restrict__ ne_ptr,
                                                     const double *__restrict__ scratch,
                                                     const uint8_t *__restrict__ mask, const double *__restrict__ F,
                                                     double lf, const double *__restrict__ v,
                                                     double *__restrict__ out, int *status) {
-    int64_t d = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (d >= N) return;
-    int64_t n = d / ND;
-    int i = int(d - n * ND);
-    double s = 0.0;
-    for (int64_t k = ne_ptr[n]; k < ne_ptr[n + 1]; ++k) s += scratch[k * ND + i];  // node n's contiguous slots
+    const int l8 = threadIdx.x & 7;
+    const int64_t n = int64_t(blockIdx.x) * (blockDim.x / 8) + threadIdx.x / 8;
+    const bool live = n < Nn;  // (every lane stays active for the sums)
+    const int64_t k0 = live ? ne_ptr[n] : 0, k1 = live ? ne_ptr[n + 1] : 0;
+    const bool own = live && l8 < ND;
+    const int64_t d = ND * n + l8;
+    const bool fixed = own && mask && mask[d];
+    const double f = own && MODE == VEC_RESIDUAL ? F[d] : 0.0;
+    double s[ND];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) s[i] = 0.0;
+    for (int64_t k = k0 + l8; k < k1; k += 8)
+#pragma unroll
+        for (int i = 0; i < ND; ++i) s[i] += scratch[k * ND + i];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) s[i] = sum8(s[i]);
+    if (!own) return;
+    double sum = s[0];
+    if constexpr (ND == 3) sum = l8 == 1 ? s[1] : (l8 == 2 ? s[2] : s[0]);
     double r;
-    if (mask && mask[d]) {
-        r = (MODE == VEC_JVP) ? v[d] : 0.0;
-    } else {
-        r = (MODE == VEC_RESIDUAL) ? s - lf * F[d] : s;
-    }
+    if (fixed) r = (MODE == VEC_JVP) ? v[d] : 0.0;
+    else r = (MODE == VEC_RESIDUAL) ? sum - lf * f : sum;
     if (!isfinite(r)) atomicOr(status, ST_NAN);
     out[d] = r;
 }
@@ -1412,7 +1425,7 @@ void launch_residual(const fem_handle *h, const double *u, const double *theta, 
         hipLaunchKernelGGL((k_element_vec<MODEL, ND, VEC_RESIDUAL>), dim3(gridE), dim3(kThreads), 0, s, g.Ne,
                            h->m.coords, h->m.conn, g.kpos, h->m.mask, h->mat, theta, u, nullptr, h->hist, scratch,
                            h->status);
-        hipLaunchKernelGGL((k_gather_vec<ND, VEC_RESIDUAL>), dim3(grid_for(g.N, 256)), dim3(256), 0, s, g.N,
+        hipLaunchKernelGGL((k_gather_vec<ND, VEC_RESIDUAL>), dim3(grid_for(g.Nn, 32)), dim3(256), 0, s, g.Nn,
                            g.ne_ptr, scratch, h->m.mask, h->m.fext, lf, nullptr, r, h->status);
     });
     FEM_HIP(hipGetLastError());
@@ -1429,7 +1442,7 @@ void launch_apply_tangent(const fem_handle *h, const double *u, const double *th
     FEM_DISPATCH_MODEL(h, {
         hipLaunchKernelGGL((k_element_vec<MODEL, ND, VEC_JVP>), dim3(gridE), dim3(kThreads), 0, s, g.Ne, h->m.coords,
                            h->m.conn, g.kpos, h->m.mask, h->mat, theta, u, v, h->hist, scratch, h->status);
-        hipLaunchKernelGGL((k_gather_vec<ND, VEC_JVP>), dim3(grid_for(g.N, 256)), dim3(256), 0, s, g.N, g.ne_ptr,
+        hipLaunchKernelGGL((k_gather_vec<ND, VEC_JVP>), dim3(grid_for(g.Nn, 32)), dim3(256), 0, s, g.Nn, g.ne_ptr,
                            scratch, h->m.mask, nullptr, 0.0, v, y, h->status);
     });
     FEM_HIP(hipGetLastError());
@@ -1443,7 +1456,7 @@ void launch_lift(const fem_handle *h, const double *u, const double *theta, cons
     FEM_DISPATCH_MODEL(h, {
         hipLaunchKernelGGL((k_element_vec<MODEL, ND, VEC_LIFT>), dim3(gridE), dim3(kThreads), 0, s, g.Ne,
                            h->m.coords, h->m.conn, g.kpos, h->m.mask, h->mat, theta, u, v, h->hist, scratch, h->status);
-        hipLaunchKernelGGL((k_gather_vec<ND, VEC_LIFT>), dim3(grid_for(g.N, 256)), dim3(256), 0, s, g.N, g.ne_ptr,
+        hipLaunchKernelGGL((k_gather_vec<ND, VEC_LIFT>), dim3(grid_for(g.Nn, 32)), dim3(256), 0, s, g.Nn, g.ne_ptr,
                            scratch, h->m.mask, nullptr, 0.0, v, y, h->status);
     });
     FEM_HIP(hipGetLastError());
@@ -1459,12 +1472,12 @@ void launch_mass(const fem_handle *h, const double *x, double *scratch, double *
     if (g.nd == 1) {
         hipLaunchKernelGGL((k_element_mass<1>), dim3(gridE), dim3(kThreads), 0, s, g.Ne, h->m.coords, h->m.conn,
                            g.kpos, x, scratch, h->status);
-        hipLaunchKernelGGL((k_gather_vec<1, VEC_MASS>), dim3(grid_for(g.N, 256)), dim3(256), 0, s, g.N, g.ne_ptr,
+        hipLaunchKernelGGL((k_gather_vec<1, VEC_MASS>), dim3(grid_for(g.Nn, 32)), dim3(256), 0, s, g.Nn, g.ne_ptr,
                            scratch, nullptr, nullptr, 0.0, nullptr, y, h->status);
     } else {
         hipLaunchKernelGGL((k_element_mass<3>), dim3(gridE), dim3(kThreads), 0, s, g.Ne, h->m.coords, h->m.conn,
                            g.kpos, x, scratch, h->status);
-        hipLaunchKernelGGL((k_gather_vec<3, VEC_MASS>), dim3(grid_for(g.N, 256)), dim3(256), 0, s, g.N, g.ne_ptr,
+        hipLaunchKernelGGL((k_gather_vec<3, VEC_MASS>), dim3(grid_for(g.Nn, 32)), dim3(256), 0, s, g.Nn, g.ne_ptr,
                            scratch, nullptr, nullptr, 0.0, nullptr, y, h->status);
     }
     FEM_HIP(hipGetLastError());
