@@ -156,6 +156,9 @@ int fem_build_pattern(const fem_mesh_desc *d, fem_handle **out, int64_t *n_dofs,
         FEM_HIP(hipDeviceGetAttribute(&h->num_cus, hipDeviceAttributeMultiprocessorCount, h->device));
         FEM_HIP(hipDeviceGetAttribute(&h->lds_bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
         FEM_HIP(hipDeviceGetAttribute(&h->clock_khz, hipDeviceAttributeWallClockRate, h->device));
+        // (cleared before the synchronous uploads below, so before any stream's first launch)
+        h->res_slots = static_cast<unsigned long long *>(fem::dev_alloc(h, fem::resident_slots_bytes(h)));
+        FEM_HIP(hipMemset(h->res_slots, 0, fem::resident_slots_bytes(h)));
         h->mat = fem::Material{d->model,   d->pmap,      d->nu,      d->bulk_ratio,
                                d->simp_p, d->simp_emin, d->simp_e0, d->yield_stress};
         const int64_t N = d->n_nodes * d->ndpn;
@@ -172,8 +175,6 @@ int fem_build_pattern(const fem_mesh_desc *d, fem_handle **out, int64_t *n_dofs,
         fem::build_graph(h, d);
         h->status = static_cast<int *>(fem::dev_alloc(h, sizeof(int)));
         FEM_HIP(hipMemset(h->status, 0, sizeof(int)));
-        h->res_slots = static_cast<unsigned long long *>(fem::dev_alloc(h, fem::resident_slots_bytes(h)));
-        FEM_HIP(hipMemset(h->res_slots, 0, fem::resident_slots_bytes(h)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_status), sizeof(int)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_scalar), sizeof(double)));
         FEM_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->host_kry), fem::kScalarsHostBytes));

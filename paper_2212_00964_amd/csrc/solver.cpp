@@ -19,8 +19,8 @@ constexpr size_t kAlign = 256;
 
 // Layout of the tangent inside the solvers.  The symmetric block layout stores half
 // the values, but the transposed reads of its lower blocks miss L2 at these sizes
-// (measured at 1M elements: 282 us and 1.83 GB fetched beyond L2 per SpMV, against
-// ~245 us for the full CSR layout), so the solvers use CSR.
+// (measured at 1M elements: 281 us and 1.86 GB fetched beyond L2 per FP32 SpMV,
+// against 184 us for the full CSR layout), so the solvers use CSR.
 constexpr int kSolverLayout = LAYOUT_CSR;
 
 // Point-Jacobi BiCGSTAB folds D^{-1} into the stored tangent (right preconditioning
