@@ -57,8 +57,8 @@ def assembly_bytes(prob, value_bytes):
 
 
 PROFILE_DIR = os.path.join(ROOT, "profiles")
-KRYLOV_SOURCES = ("paper_2212_00964_amd/csrc/linalg.hip", "paper_2212_00964_amd/csrc/internal.h",
-                  "paper_2212_00964_amd/csrc/lanes.h")
+KRYLOV_SOURCES = ("paper_2212_00964_amd/csrc/linalg.hip", "paper_2212_00964_amd/csrc/bicg_rules.h",
+                  "paper_2212_00964_amd/csrc/internal.h", "paper_2212_00964_amd/csrc/lanes.h")
 ASSEMBLY_SOURCES = ("paper_2212_00964_amd/csrc/element.hip", "paper_2212_00964_amd/csrc/internal.h",
                     "paper_2212_00964_amd/csrc/lanes.h")
 
@@ -287,7 +287,7 @@ def assembly_roofline(fem, prob, u, reps=5):
     nbytes = assembly_bytes(prob, 4)
     achieved = nbytes / (ms * 1e-3) / 1e9
     del vals
-    return {"bound": "hbm", "kernel": "k_element_tangent + k_gather_node (FP32 values, CSR)", "achieved": achieved,
+    return {"bound": "hbm", "kernel": "k_tangent_blocks + k_gather_rows (FP32 values, CSR)", "achieved": achieved,
             "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS,
             "traffic": measured_traffic("assembly_nh_tensile_100x100x100.md", ASSEMBLY_SOURCES),
             "avg_launch_us": 1e3 * ms, "launches": reps, "bytes_per_launch": nbytes,
