@@ -941,8 +941,7 @@ __global__ __launch_bounds__(256) void k_extract_binv(int64_t Nn, const int64_t 
 // reference cube by J^{-T}) and P, Q, R vectors of node a, quadrature weight included:
 //   neo-Hookean: H = F^{-T} J^{-T}, F = F J^{-T}, h = H dN_a, f = F dN_a,
 //                P = aw h - c23 f, Q = bw h, R = -c23 h, M = cw J^{-1} J^{-T}
-//   J2:          H = J^{-T}, F = s J^{-T}, P = lw h, Q = mw h, R = -bw f, M = mw J^{-1} J^{-T}
-//   linear:      as J2 without F
+//   linear:      H = J^{-T}, P = lw h, Q = mw h, M = mw J^{-1} J^{-T}
 //   Poisson:     M only.
 // k_tangent_blocks: a wavefront takes 8 (FP32) or 4 (FP64) elements; lane q evaluates
 // Gauss point q once and leaves those numbers (28 at most) in LDS; then 16 lanes per
@@ -974,8 +973,8 @@ template <int MODEL, int ND, typename T>
 __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_blocks(
     int64_t Ne, const double *__restrict__ coords, const int32_t *__restrict__ conn,
     const int32_t *__restrict__ kpos, Material mat, const double *__restrict__ theta, const double *__restrict__ u,
-    const double *__restrict__ hist, T *__restrict__ ke, int *status) {
-    constexpr bool kNonlinear = MODEL == FEM_NEO_HOOKEAN || MODEL == FEM_J2_PLASTIC;
+    T *__restrict__ ke, int *status) {
+    constexpr bool kNonlinear = MODEL == FEM_NEO_HOOKEAN;
     constexpr int NF = 3 + (kNonlinear ? ND : 0), BS = ND * ND, S = state_size<MODEL>(), W = 16 / int(sizeof(T));
     constexpr int E = wave_elems<T>(), RI = rows_at_once<ND, T>(), RS = RI * ND;
     constexpr int kLds = E * 8 * S > 64 * NF ? E * 8 * S : 64 * NF;
@@ -1083,19 +1082,6 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
             put_metric(18, cw);
             out[24] = wq * st.alpha;
             out[25] = wq * st.beta;
-        } else if constexpr (MODEL == FEM_J2_PLASTIC) {
-            J2State<T> st;
-            j2_state(mat, mod, G, hist + (e * 8 + q) * 12, st);
-            put_matrix(0, B);
-            const T D[3][3] = {{st.dev[0], st.dev[5], st.dev[4]}, {st.dev[5], st.dev[1], st.dev[3]},
-                               {st.dev[4], st.dev[3], st.dev[2]}};
-            T R[3][3];
-            times_b(D, R);
-            put_matrix(9, R);
-            put_metric(18, wq * st.mup);
-            out[24] = wq * st.lw;
-            out[25] = wq * st.mup;
-            out[26] = wq * st.beta;
         } else if constexpr (MODEL == FEM_LINEAR_ELASTIC) {
             const T nu = T(mat.nu);
             const T lw = wq * mod * nu / ((T(1) + nu) * (T(1) - T(2) * nu)), mw = wq * mod / (T(2) * (T(1) + nu));
@@ -1183,9 +1169,6 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
                             if constexpr (MODEL == FEM_NEO_HOOKEAN) {
                                 P = st[24] * h[i] - fi;
                                 R = -h[i];
-                            } else if constexpr (MODEL == FEM_J2_PLASTIC) {
-                                P = st[24] * h[i];
-                                R = -st[26] * fi;
                             } else {
                                 P = st[15] * h[i];
                             }
@@ -1262,7 +1245,8 @@ constexpr int kGatherMaxDeg = 32;  // neighbours of a node on the row path
 constexpr int kGatherMaxInc = 8;   // and its elements
 
 // The rows of two consecutive nodes per wavefront, 32 lanes each.  The slots of a node
-// (and of the next one) are one contiguous run of k_tangent_blocks' output: the wavefront
+// (and of the next one) are one contiguous run of the element kernel's output (BLOCKS: of
+// k_element_tangent's, block after block; else k_tangent_blocks', row after row): the wavefront
 // copies it to LDS, lane j of a half sums what belongs to neighbour block j -- a 64-bit
 // mask per block (bit 8 * slot + b), built from the slots' target bytes, lists its
 // contributions in element order -- applies the symmetric Dirichlet elimination and
@@ -1270,7 +1254,7 @@ constexpr int kGatherMaxInc = 8;   // and its elements
 // read-modify-write of an image and no block barrier.
 // What bounds it: at 100^3 in FP32 its 2.3 GB in and 1.0 GB out, 5.1 TB/s (650 us; slot by
 // slot additions into an LDS image of the rows took 1,079 us); FP64, 37x29x23: 39 -> 28 us.
-template <int ND, int LAYOUT, typename T>
+template <int ND, int LAYOUT, bool BLOCKS, typename T>
 __global__ __launch_bounds__(kThreads) void k_gather_rows(int64_t Nn, const int64_t *__restrict__ node_ptr,
                                                           const uint8_t *__restrict__ nb_bits,
                                                           const int64_t *__restrict__ ne_ptr,
@@ -1335,11 +1319,11 @@ __global__ __launch_bounds__(kThreads) void k_gather_rows(int64_t Nn, const int6
     while (m) {  // ascending slots: element order
         const int l = __builtin_ctzll(m);
         m &= m - 1;
-        const T *o = mine + (l >> 3) * kSlot + (l & 7) * ND;
+        const T *o = mine + (l >> 3) * kSlot + (l & 7) * (BLOCKS ? BS : ND);
 #pragma unroll
         for (int i = 0; i < ND; ++i)
 #pragma unroll
-            for (int c = 0; c < ND; ++c) acc[i * ND + c] += o[i * 8 * ND + c];
+            for (int c = 0; c < ND; ++c) acc[i * ND + c] += o[i * (BLOCKS ? ND : 8 * ND) + c];
     }
     if (split)
 #pragma unroll
@@ -1523,6 +1507,23 @@ void launch_vjp(const fem_handle *h, const double *u, const double *theta, const
     FEM_HIP(hipGetLastError());
 }
 
+// The element blocks of the row gather.  J2 keeps the form that evaluates the return map at
+// the strains of its residual, rounding included: with the factorised gradients a point that
+// the history put on the yield surface could be elastic in one and plastic in the other, and
+// past the limit load CG then met matrices it could not solve (48x48x96 cylinder, loading and
+// unloading in 20 steps: 20,000 iterations without convergence; with this form 5.5 s).
+template <int MODEL, int ND, typename T>
+static void launch_element_blocks(const fem_handle *h, const double *u, const double *theta, T *ke, hipStream_t s) {
+    const Graph &g = h->g;
+    if constexpr (MODEL == FEM_J2_PLASTIC)
+        hipLaunchKernelGGL((k_element_tangent<MODEL, ND, T>), dim3(grid_for(g.Ne, kElemsPerBlock)), dim3(kThreads), 0, s,
+                           g.Ne, h->m.coords, h->m.conn, g.kpos, h->mat, theta, u, h->hist, ke, h->status);
+    else
+        hipLaunchKernelGGL((k_tangent_blocks<MODEL, ND, T>),
+                           dim3((grid_for(g.Ne, wave_elems<T>() * kThreads / 64) + 7) / 8 * 8), dim3(kThreads), 0, s,
+                           g.Ne, h->m.coords, h->m.conn, g.kpos, h->mat, theta, u, ke, h->status);
+}
+
 template <typename T>
 void launch_tangent(const fem_handle *h, const double *u, const double *theta, T *ke, T *values, T *dinv,
                     hipStream_t s, int layout, int precond) {
@@ -1534,17 +1535,14 @@ void launch_tangent(const fem_handle *h, const double *u, const double *theta, T
     const bool by_rows = g.tgt != nullptr && g.max_deg <= kGatherMaxDeg && g.max_inc <= kGatherMaxInc;
     FEM_DISPATCH_MODEL(h, {
         if (by_rows) {
-            hipLaunchKernelGGL((k_tangent_blocks<MODEL, ND, T>),
-                               dim3((grid_for(g.Ne, wave_elems<T>() * kThreads / 64) + 7) / 8 * 8), dim3(kThreads), 0,
-                               s, g.Ne, h->m.coords, h->m.conn, g.kpos, h->mat, theta, u, h->hist,
-                               ke, h->status);
+            (launch_element_blocks<MODEL, ND, T>(h, u, theta, ke, s));
             const dim3 grid(grid_for(g.Nn, 2 * kThreads / 64));
             if (layout == LAYOUT_SYM)
-                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_SYM, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
+                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_SYM, MODEL == FEM_J2_PLASTIC, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
                                    g.nb_bits, g.ne_ptr, g.tgt, g.bdiag, g.up_base, h->m.mask, ke, values, dinv, bj,
                                    h->status);
             else
-                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_CSR, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
+                hipLaunchKernelGGL((k_gather_rows<ND, LAYOUT_CSR, MODEL == FEM_J2_PLASTIC, T>), grid, dim3(kThreads), 0, s, g.Nn, g.node_ptr,
                                    g.nb_bits, g.ne_ptr, g.tgt, g.bdiag, g.up_base, h->m.mask, ke, values, dinv, bj,
                                    h->status);
         } else {

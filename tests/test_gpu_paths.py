@@ -197,3 +197,17 @@ def test_resident_rows_beyond_registers(law, shape, precision, krylov, relabel):
     u_sep, _ = prob.newton_solve(profile_spmv=1, **opts)
     assert_parity(host(u), host(u_sep), 4e-6)
     prob.close()
+
+
+def test_j2_path_past_the_limit_load():
+    """Loading and unloading of the 48x48x96 cylinder: Newton needs a tangent that takes the
+    residual's side at every point on the yield surface.  Known stress history: peak 258.7,
+    end -254.1 (0.1 of the last digit given)."""
+    import pathlib
+    import sys
+
+    sys.path.insert(0, str(pathlib.Path(__file__).resolve().parent.parent))
+    import bench
+
+    out = bench.j2_path(fem, gen, 48, 96, fem.PRECOND_JACOBI, fem.PREC_FP64, 0, time_limit_s=60.0)
+    assert abs(max(out["avg_sigma_zz"]) - 258.7) < 0.06 and abs(out["avg_sigma_zz"][-1] + 254.1) < 0.06
