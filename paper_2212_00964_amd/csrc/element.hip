@@ -359,6 +359,8 @@ __device__ __forceinline__ void load_node(const double *coords, const int32_t *c
 constexpr double kFar = 0.26794919243112270647;  // r = (1 - g) / (1 + g) = 2 - sqrt(3), g = 1 / sqrt(3)
 // (p^2 / 2)^3, p^2 = (2 + sqrt(3)) / 6: the factors left out of the determinant
 constexpr double kCornerDet = 0.03008145955644280059;
+// (lp^2 / 2) (2 / p^2)^2 = 2 / p^2 with lp = p: the rule's weight of a point of the tangent
+constexpr double kPointWeight = 3.21539030917347247767;
 
 // Derivatives along the three directions at this lane's point of the field with value v at
 // this lane's node, without their factors s_k p^2 / 2.
@@ -943,107 +945,96 @@ __global__ __launch_bounds__(256) void k_extract_binv(int64_t Nn, const int64_t 
 //                P = aw h - c23 f, Q = bw h, R = -c23 h, M = cw J^{-1} J^{-T}
 //   linear:      H = J^{-T}, P = lw h, Q = mw h, M = mw J^{-1} J^{-T}
 //   Poisson:     M only.
-// k_tangent_blocks: a wavefront takes 8 (FP32) or 4 (FP64) elements; lane q evaluates
-// Gauss point q once and leaves those numbers (28 at most) in LDS; then 16 lanes per
-// element, two per node a (one for each half q2 of the points), sum C over the rule's
-// factors -- dN_b,0 does not depend on q0, dN_b,1 not on q1, dN_b,2 not on q2 up to its
-// sign, so 8 running sums per entry (i, k) hold what the 8 columns b need -- contract
-// them with the one-dimensional shape values once and write the slot's row block, rows
-// i one after the other.  Exchanges stay inside the wavefront: no block barrier.
-// What bounds it: at 100^3 in FP32 the 2.4 GB it writes (878 us; 595 us when its stores
-// stay in L2; 272 M vector instructions, 0.44 ms at full issue).  The element matrices
-// with 8 lanes per element and all exchanges of a point through LDS and block barriers
-// took 1,129 us.  FP64, 37x29x23 neo-Hookean: 86 -> 53 us, two rounds of wavefronts each
-// waiting on the chain of divisions and the cube root of its points.
-// Whole tangent, element kernel and gather, before -> now: 100^3 FP32 2,097 -> 1,537 us
-// (linear 1,864 -> 1,442, Poisson 1,037 -> 385), FP64 3,849 -> 2,992 (Poisson 1,310 ->
-// 564); 40^3 FP32 156 -> 88, FP64 317 -> 226.
-template <int MODEL>
-constexpr int state_size() {
-    return MODEL == FEM_POISSON ? 8 : (MODEL == FEM_LINEAR_ELASTIC ? 20 : 28);
-}
-// Elements per wavefront, and the rows i that a lane sums at a time: FP64 takes them one by
-// one (24 running sums in 48 registers; all 72 would leave one wavefront per SIMD).
-template <typename T>
-constexpr int wave_elems() { return sizeof(T) == 4 ? 8 : 4; }
-template <int ND, typename T>
-constexpr int rows_at_once() { return sizeof(T) == 4 ? ND : 1; }
+// k_tangent_blocks: a wavefront takes 8 (FP32 values) or 4 (FP64 values) elements; a lane is
+// one corner of an element's cube as in k_element_vec, evaluates its Gauss point once and
+// leaves H, F c23, aw, bw (linear: H, lw, mw; Poisson: M) in LDS -- M dN_a is (3/2) (F c23)^T h, or
+// H^T Q; then 16 lanes per element, two per node a (one for each half q2 of the points), sum C
+// over the rule's factors -- dN_b,0 does not depend on q0, dN_b,1 not on q1, dN_b,2 not on q2 up
+// to its sign, so 8 running sums per entry (i, k) hold what the 8 columns b need -- contract
+// them with the one-dimensional shape values once and write the slot's row block, rows i
+// one after the other.  Exchanges stay inside the wavefront: no block barrier.
+// Arithmetic is FP64 for both types of values, and every entry is rounded once, when it is
+// stored.  The sums of the factorised form are larger than the entries they leave; in FP32
+// the blocks (a, b) and (b, a) round apart and the entries are further off than summed block by
+// block.  |dK| / |K| and |K - K^T| / |K| of the FP32 tangent, factorised in FP32 / block by block
+// in FP32 (k_element_tangent) / now: 40^3 neo-Hookean 1.28e-7, 5.1e-8 / 9.3e-8, 6.2e-8 / 4.0e-8, 0;
+// 120x60x30 densities 9.7e-9, 1.4e-9 / 4.8e-9, 2.1e-9 / 2.1e-9, 0.
+// What bounds it: at 100^3 with FP32 values instruction issue (4,000 vector instructions per
+// wavefront, 0.8 ms, not all of it under the 2.4 GB it writes; FP32 sums took 0.24 ms less).
+// The 72 sums of all three rows at once spill (2.1 ms).  With FP64 values the 4.8 GB.
+// Whole tangent, element kernel and gather, with k_element_tangent -> now, us: 100^3 FP32
+// 1,727 -> 1,773, FP64 3,776 -> 2,650 (linear 1,522 -> 1,507 and 3,570 -> 2,493, Poisson 492 -> 380
+// and 1,291 -> 503); 37x29x23 64 -> 58 and 126 -> 69; 10^3 28.6 -> 21.5 and 38.6 -> 20.3.
 
-template <int MODEL, int ND, typename T>
-__global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_blocks(
+// Numbers of a point in LDS: an odd count (one is unused for neo-Hookean and Poisson), with which
+// the two elements and two halves that 32 lanes read at a time start in different banks (20
+// for neo-Hookean: 64 us instead of 58 with FP32 values and 76 instead of 69 with FP64 at 37x29x23).
+template <int MODEL>
+constexpr int point_numbers() { return MODEL == FEM_POISSON ? 7 : (MODEL == FEM_LINEAR_ELASTIC ? 11 : 21); }
+// Elements per wavefront: with FP64 values twice as many would leave two wavefronts per SIMD.
+template <typename TV>
+constexpr int wave_elems() { return sizeof(TV) == 4 ? 8 : 4; }
+
+template <int MODEL, int ND, typename TV>
+__global__ __launch_bounds__(kThreads, MODEL == FEM_NEO_HOOKEAN ? 2 : 3) void k_tangent_blocks(
     int64_t Ne, const double *__restrict__ coords, const int32_t *__restrict__ conn,
     const int32_t *__restrict__ kpos, Material mat, const double *__restrict__ theta, const double *__restrict__ u,
-    T *__restrict__ ke, int *status) {
+    TV *__restrict__ ke, int *status) {
+    typedef double T;
     constexpr bool kNonlinear = MODEL == FEM_NEO_HOOKEAN;
-    constexpr int NF = 3 + (kNonlinear ? ND : 0), BS = ND * ND, S = state_size<MODEL>(), W = 16 / int(sizeof(T));
-    constexpr int E = wave_elems<T>(), RI = rows_at_once<ND, T>(), RS = RI * ND;
-    constexpr int kLds = E * 8 * S > 64 * NF ? E * 8 * S : 64 * NF;
-    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-    // the nodes' values, then the points' numbers; and one row i of 32 slots on its way out
-    constexpr int kRow = 8 * ND, kOut = ND == 1 ? 0 : 32 * kRow;
-    __shared__ __align__(16) T lds[kThreads / 64][kLds + kOut];
-    __shared__ int32_t skpos[kThreads / 64][E * 8];
+    constexpr int BS = ND * ND, S = point_numbers<MODEL>(), W = 16 / int(sizeof(TV));
+    constexpr int E = wave_elems<TV>();
+    typedef TV vec __attribute__((ext_vector_type(16 / sizeof(TV))));
+    // the points' numbers; and one row i of 32 slots on its way out
+    constexpr int kRow = 8 * ND, kOut = ND == 1 ? 2 : 32 * kRow;
+    __shared__ __align__(16) T lds[kThreads / 64][E * 8 * S];
+    __shared__ __align__(16) TV out_lds[kThreads / 64][kOut];
     const int wave = threadIdx.x / 64, lane = threadIdx.x & 63;
     // Blocks of one XCD take adjacent elements: the slots of a node that share cache lines are
     // then completed in one L2 instead of leaving it as partial lines.
     const int64_t blk = int64_t(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     const int64_t ew = (blk * (kThreads / 64) + wave) * E;  // first element of the wavefront
     if (ew >= Ne) return;  // wave-uniform; there are no block barriers
-    T *node_vals = lds[wave];
+    int32_t my_slot;  // of this lane's node, -1 past the mesh
+    // that of node a of element el (every lane takes part)
+    auto slot = [&](int el, int a) -> int32_t {
+        const int c = a ^ ((a >> 1) & 1);
+        return __shfl(my_slot, el * 8 + (c ^ ((c & 4) ? 3 : 0)), 64);
+    };
     {
         // lanes past the wavefront's or the mesh's elements repeat one and store nothing
         const int el = (lane >> 3) % E;
         const bool valid = lane < 8 * E && ew + el < Ne;
         ElemIds id;
-        id.a = lane & 7;
+        // corner of this lane, its node and its Gauss point as in k_element_vec
+        const int l8 = lane & 7, c = l8 ^ ((l8 & 4) ? 3 : 0);
+        id.a = c ^ ((c >> 1) & 1);
         id.el = el;
         id.valid = valid;
         id.e = ew + el < Ne ? ew + el : Ne - 1;
         const int64_t e = id.e;
-        const int q = id.a;
         T X[3], U[ND];
         load_node<ND, kNonlinear ? LOAD_FIELD | LOAD_REL : LOAD_COORDS>(coords, conn, u, nullptr, id, X, U);
-        const T mod = T(modulus(mat, theta[e]));
+        const T mod = modulus(mat, theta[e]);
+        // (the slots too, before the first store: a load after one would wait for it)
+        my_slot = kpos[e * 8 + id.a];
+        if (!valid) my_slot = -1;
+        // J and the gradients without the factor p^2 / 2 of every column and the sign s_k of column k
+        T J[3][3], Gr[3][3] = {};
 #pragma unroll
-        for (int i = 0; i < 3; ++i) node_vals[lane * NF + i] = X[i];
+        for (int i = 0; i < 3; ++i) corner_grad(X[i], J[i]);
         if constexpr (kNonlinear)
 #pragma unroll
-            for (int i = 0; i < ND; ++i) node_vals[lane * NF + 3 + i] = U[i];
-        // (the slots too, before the first store: a load after one would wait for it)
-        if (lane < 8 * E) skpos[wave][lane] = valid ? kpos[e * 8 + id.a] : -1;
-        wave_lds_handoff();
-        T J[3][3] = {}, Gr[3][3] = {};
-#pragma unroll 2
-        for (int b = 0; b < 8; ++b) {
-            T dN[3];
-            ref_grad<T>(b, q, dN);
-            const T *nb = node_vals + (lane - q + b) * NF;
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    J[i][j] = fma(nb[i], dN[j], J[i][j]);
-                    if constexpr (kNonlinear) Gr[i][j] = fma(nb[3 + i], dN[j], Gr[i][j]);
-                }
-        }
-        const T d = det3(J);
+            for (int i = 0; i < ND; ++i) corner_grad(U[i], Gr[i]);
+        const T dj = det3(J);
+        const T d = (__popc(c) & 1) ? kCornerDet * dj : -kCornerDet * dj;
         bool mat_ok = true;
-        T B[3][3];  // J^{-T}
-        inv_transpose3(J, d, B);
-        // Weight of the point with the factors common to all columns b: every 1-D shape value
-        // below is taken relative to the larger one, lp = (1 + 1/sqrt(3)) / 2.
-        const T wq = T(0.5 * 0.78867513459481288225 * 0.78867513459481288225) * d;
-        T out[S];
-#pragma unroll
-        for (int c = 0; c < S; ++c) out[c] = T(0);
-        auto put_metric = [&](int at, T w) {  // w J^{-1} J^{-T}: (00, 11, 22, 12, 02, 01)
-            constexpr int pr[6][2] = {{0, 0}, {1, 1}, {2, 2}, {1, 2}, {0, 2}, {0, 1}};
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-                const int r = pr[c][0], t = pr[c][1];
-                out[at + c] = w * (B[0][r] * B[0][t] + B[1][r] * B[1][t] + B[2][r] * B[2][t]);
-            }
-        };
+        T B[3][3];  // J^{-T}, likewise
+        inv_transpose3(J, dj, B);
+        // Weight of the point: the factors common to all columns b (every 1-D shape value below is
+        // taken relative to the larger one) and the (2 / p^2)^2 left out of the two B of each term.
+        const T wq = T(kPointWeight) * d;
+        T out[S] = {};
         auto put_matrix = [&](int at, const T A[3][3]) {
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -1062,10 +1053,13 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
             for (int i = 0; i < 3; ++i)
 #pragma unroll
                 for (int j = 0; j < 3; ++j) G[i][j] = Gr[i][0] * B[j][0] + Gr[i][1] * B[j][1] + Gr[i][2] * B[j][2];
-        // The third reference axis reversed where q2 = 0: columns b2 = 0 then enter with the same
-        // sign as b2 = 1.
+        // The signs s_0 and s_1 of the columns.  The third column stays without: its axis is reversed
+        // where q2 = 0, so that columns b2 = 0 enter with the same sign as b2 = 1.
 #pragma unroll
-        for (int i = 0; i < 3; ++i) B[i][2] = (q & 4) ? B[i][2] : -B[i][2];
+        for (int i = 0; i < 3; ++i) {
+            B[i][0] = (c & 1) ? B[i][0] : -B[i][0];
+            B[i][1] = (c & 2) ? B[i][1] : -B[i][1];
+        }
         if constexpr (MODEL == FEM_NEO_HOOKEAN) {
             NHState<T> st;
             mat_ok = nh_state(G, mod, T(mat.bulk_ratio), st);
@@ -1079,31 +1073,28 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
 #pragma unroll
                 for (int r = 0; r < 3; ++r) R[i][r] *= c23;
             put_matrix(9, R);
-            put_metric(18, cw);
-            out[24] = wq * st.alpha;
-            out[25] = wq * st.beta;
+            out[18] = wq * st.alpha;
+            out[19] = wq * st.beta;
         } else if constexpr (MODEL == FEM_LINEAR_ELASTIC) {
             const T nu = T(mat.nu);
             const T lw = wq * mod * nu / ((T(1) + nu) * (T(1) - T(2) * nu)), mw = wq * mod / (T(2) * (T(1) + nu));
             put_matrix(0, B);
-            put_metric(9, mw);
-            out[15] = lw;
-            out[16] = mw;
+            out[9] = lw;
+            out[10] = mw;
         } else {
-            put_metric(0, wq * mod);
+            constexpr int pr[6][2] = {{0, 0}, {1, 1}, {2, 2}, {1, 2}, {0, 2}, {0, 1}};
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const int r = pr[q][0], t = pr[q][1];
+                out[q] = wq * mod * (B[0][r] * B[0][t] + B[1][r] * B[1][t] + B[2][r] * B[2][t]);
+            }
         }
         if (valid && (!(d > T(0)) || !mat_ok))
             atomicOr(status, (!(d > T(0)) ? ST_MESH : 0) | (!mat_ok ? ST_INVERTED : 0));
-        wave_lds_handoff();  // the nodes' values are read
         if (lane < 8 * E) {
-            vec *dst = reinterpret_cast<vec *>(lds[wave] + lane * S);
+            T *dst = lds[wave] + (el * 8 + c) * S;
 #pragma unroll
-            for (int c = 0; c < S / W; ++c) {
-                vec v;
-#pragma unroll
-                for (int w = 0; w < W; ++w) v[w] = out[c * W + w];
-                dst[c] = v;
-            }
+            for (int q = 0; q < S; ++q) dst[q] = out[q];
         }
         wave_lds_handoff();
     }
@@ -1116,15 +1107,14 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
 #pragma unroll 1
     for (int round = 0; round < E / 4; ++round) {
         const int el = 4 * round + (lane >> 4);
-        const bool valid = ew + el < Ne;
         int at = (el * 8 + 4 * half) * S;
 #pragma unroll
-        for (int i0 = 0; i0 < ND; i0 += RI) {
-            // (an opaque offset: the numbers are read from LDS again for each group of rows
+        for (int i = 0; i < ND; ++i) {
+            // (an opaque offset: the numbers are read from LDS again for every row
             // instead of being carried along in registers)
             asm volatile("" : "+v"(at));
             const T *pt = lds[wave] + at;
-            T S0[2][RS], S1[2][RS], S2[2][2][RS];
+            T S0[2][ND], S1[2][ND], S2[2][2][ND];
 #pragma unroll
             for (int q1 = 0; q1 < 2; ++q1)
 #pragma unroll
@@ -1132,57 +1122,53 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
                     const T *st = pt + (2 * q1 + q0) * S;
                     const T l0 = (ax == bool(q0)) ? lp : lm, l1 = (ay == bool(q1)) ? lp : lm;
                     const T dN[3] = {hx * l1 * l2, hy * l0 * l2, hz * l0 * l1};
-                    constexpr int kM = MODEL == FEM_POISSON ? 0 : (MODEL == FEM_LINEAR_ELASTIC ? 9 : 18);
-                    const T *M = st + kM;
-                    const T gb[3] = {M[0] * dN[0] + M[5] * dN[1] + M[4] * dN[2],
-                                     M[5] * dN[0] + M[1] * dN[1] + M[3] * dN[2],
-                                     M[4] * dN[0] + M[3] * dN[1] + M[2] * dN[2]};
-                    // the running sums of the three directions, as the start of this point's terms
-                    auto start = [&](int ik, int r) -> T {
-                        if (r == 0) return q0 == 0 ? T(0) : S0[q1][ik];
-                        if (r == 1) return q1 == 0 ? T(0) : S1[q0][ik];
-                        return T(0);
-                    };
-                    auto put = [&](int ik, int r, T v) {
-                        if (r == 0) S0[q1][ik] = v;
-                        else if (r == 1) S1[q0][ik] = v;
-                        else S2[q0][q1][ik] = v;
+                    // the running sums of the three directions; first: they start at this point
+                    auto first = [&](int r) { return r == 2 || (r == 0 ? q0 : q1) == 0; };
+                    auto sum = [&](int k, int r) -> T { return r == 0 ? S0[q1][k] : S1[q0][k]; };
+                    auto put = [&](int k, int r, T v) {
+                        if (r == 0) S0[q1][k] = v;
+                        else if (r == 1) S1[q0][k] = v;
+                        else S2[q0][q1][k] = v;
                     };
                     if constexpr (MODEL == FEM_POISSON) {
+                        const T gb[3] = {st[0] * dN[0] + st[5] * dN[1] + st[4] * dN[2],
+                                         st[5] * dN[0] + st[1] * dN[1] + st[3] * dN[2],
+                                         st[4] * dN[0] + st[3] * dN[1] + st[2] * dN[2]};
 #pragma unroll
-                        for (int r = 0; r < 3; ++r) put(0, r, start(0, r) + gb[r]);
+                        for (int r = 0; r < 3; ++r) put(0, r, first(r) ? gb[r] : sum(0, r) + gb[r]);
                     } else {
                         constexpr bool kF = MODEL != FEM_LINEAR_ELASTIC;
                         const T *H = st, *F = st + 9;
                         T h[3], Q[3];
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            h[i] = H[3 * i] * dN[0] + H[3 * i + 1] * dN[1] + H[3 * i + 2] * dN[2];
-                            Q[i] = st[MODEL == FEM_LINEAR_ELASTIC ? 16 : 25] * h[i];
+                        for (int k = 0; k < 3; ++k) {
+                            h[k] = H[3 * k] * dN[0] + H[3 * k + 1] * dN[1] + H[3 * k + 2] * dN[2];
+                            Q[k] = st[kF ? 19 : 10] * h[k];
+                        }
+                        T gb[3];  // M dN_a
+#pragma unroll
+                        for (int r = 0; r < 3; ++r)
+                            gb[r] = kF ? T(1.5) * (F[r] * h[0] + F[3 + r] * h[1] + F[6 + r] * h[2])
+                                       : H[r] * Q[0] + H[3 + r] * Q[1] + H[6 + r] * Q[2];
+                        const T *Hi = H + 3 * i, *Fi = F + 3 * i;
+                        const T fi = kF ? Fi[0] * dN[0] + Fi[1] * dN[1] + Fi[2] * dN[2] : T(0);
+                        T P, R = T(0);
+                        if constexpr (MODEL == FEM_NEO_HOOKEAN) {
+                            P = st[18] * h[i] - fi;
+                            R = -h[i];
+                        } else {
+                            P = st[9] * h[i];
                         }
 #pragma unroll
-                        for (int c = 0; c < RI; ++c) {
-                            const int i = RI == ND ? c : i0;
-                            const T *Hi = H + 3 * i, *Fi = F + 3 * i;
-                            const T fi = kF ? Fi[0] * dN[0] + Fi[1] * dN[1] + Fi[2] * dN[2] : T(0);
-                            T P, R = T(0);
-                            if constexpr (MODEL == FEM_NEO_HOOKEAN) {
-                                P = st[24] * h[i] - fi;
-                                R = -h[i];
-                            } else {
-                                P = st[15] * h[i];
+                        for (int k = 0; k < 3; ++k)
+#pragma unroll
+                            for (int r = 0; r < 3; ++r) {
+                                T v;
+                                if (first(r)) v = k == i ? fma(P, H[3 * k + r], gb[r]) : P * H[3 * k + r];
+                                else v = fma(P, H[3 * k + r], k == i ? sum(k, r) + gb[r] : sum(k, r));
+                                if constexpr (kF) v = fma(R, F[3 * k + r], v);
+                                put(k, r, fma(Q[k], Hi[r], v));
                             }
-#pragma unroll
-                            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                                for (int r = 0; r < 3; ++r) {
-                                    T v = start(3 * c + k, r);
-                                    if (k == i) v += gb[r];
-                                    v = fma(P, H[3 * k + r], v);
-                                    if constexpr (kF) v = fma(R, F[3 * k + r], v);
-                                    put(3 * c + k, r, fma(Q[k], Hi[r], v));
-                                }
-                        }
                     }
                 }
             // Columns b = (b0, b1, b2): dN_b,0 = s0 l_b1 l_b2 / 2 and so on; with every l over lp (1 or
@@ -1190,52 +1176,49 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 3 : 4) void k_tangent_bl
             //   A[b0][b1] = s0 sum_q1 l_b1 S0 + s1 sum_q0 l_b0 S1,  B[b0][b1] = sum l_b0 l_b1 S2
             // for b2 = h, and l_b2(h) A - B for the other.  Lane h keeps b2 = h and hands its part
             // of the other to its neighbour.  Nodes in HEX8 order: (b0, b1) = 00, 10, 11, 01.
+            T o[4 * ND];
 #pragma unroll
-            for (int c = 0; c < RI; ++c) {
-                T o[4 * ND];
+            for (int k = 0; k < ND; ++k) {
+                const T u0 = fma(t, S0[1][k], S0[0][k]), u1 = fma(t, S0[0][k], S0[1][k]);
+                const T w0 = fma(t, S1[1][k], S1[0][k]), w1 = fma(t, S1[0][k], S1[1][k]);
+                const T v00 = fma(t, S2[1][0][k], S2[0][0][k]), v10 = fma(t, S2[0][0][k], S2[1][0][k]);
+                const T v01 = fma(t, S2[1][1][k], S2[0][1][k]), v11 = fma(t, S2[0][1][k], S2[1][1][k]);
+                const T A[4] = {-u0 - w0, u0 - w1, u1 + w1, w0 - u1};
+                const T B[4] = {fma(t, v01, v00), fma(t, v11, v10), fma(t, v10, v11), fma(t, v00, v01)};
 #pragma unroll
-                for (int k = 0; k < ND; ++k) {
-                    const int ik = c * ND + k;
-                    const T u0 = fma(t, S0[1][ik], S0[0][ik]), u1 = fma(t, S0[0][ik], S0[1][ik]);
-                    const T w0 = fma(t, S1[1][ik], S1[0][ik]), w1 = fma(t, S1[0][ik], S1[1][ik]);
-                    const T v00 = fma(t, S2[1][0][ik], S2[0][0][ik]), v10 = fma(t, S2[0][0][ik], S2[1][0][ik]);
-                    const T v01 = fma(t, S2[1][1][ik], S2[0][1][ik]), v11 = fma(t, S2[0][1][ik], S2[1][1][ik]);
-                    const T A[4] = {-u0 - w0, u0 - w1, u1 + w1, w0 - u1};
-                    const T B[4] = {fma(t, v01, v00), fma(t, v11, v10), fma(t, v10, v11), fma(t, v00, v01)};
+                for (int b = 0; b < 4; ++b)
+                    o[b * ND + k] = (A[b] + B[b]) + dpp_read<kDppXor1>(fma(t, A[b], -B[b]));
+            }
+            // Row i of a slot is 8 * ND consecutive values.  The wavefront's 32 rows go through
+            // LDS so that neighbouring lanes store neighbouring 16-byte pieces (stored straight
+            // from each lane's registers they took as long again as the whole kernel).
+            if constexpr (ND == 1) {
+                const int32_t k = slot(el, a);
+                if (k >= 0) {
+                    TV *row = ke + int64_t(k) * 8 * BS + half * 4;
 #pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        o[b * ND + k] = (A[b] + B[b]) + dpp_read<kDppXor1>(fma(t, A[b], -B[b]));
+                    for (int v = 0; v < 4; ++v) row[v] = TV(o[v]);
                 }
-                // Row i of a slot is 8 * ND consecutive values.  The wavefront's 32 rows go through
-                // LDS so that neighbouring lanes store neighbouring 16-byte pieces (stored straight
-                // from each lane's registers they took as long again as the whole kernel).
-                if constexpr (kOut == 0) {
-                    if (valid) {
-                        T *row = ke + int64_t(skpos[wave][32 * round + (lane >> 1)]) * 8 * BS + half * 4;
+            } else {
+                TV *stage = out_lds[wave];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) row[v] = o[v];
-                    }
-                } else {
-                    T *stage = lds[wave] + kLds;
+                for (int v = 0; v < 4 * ND / W; ++v) {
+                    vec x;
 #pragma unroll
-                    for (int v = 0; v < 4 * ND / W; ++v) {
-                        vec x;
-#pragma unroll
-                        for (int w = 0; w < W; ++w) x[w] = o[v * W + w];
-                        reinterpret_cast<vec *>(stage + lane * 4 * ND)[v] = x;
-                    }
-                    wave_lds_handoff();
-                    constexpr int kP = kRow / W;  // pieces per row
-#pragma unroll
-                    for (int t = 0; t < 32 * kP / 64; ++t) {
-                        const int p = lane + 64 * t, sl = p / kP;
-                        const int32_t k = skpos[wave][32 * round + sl];
-                        const vec x = reinterpret_cast<const vec *>(stage)[p];
-                        if (k >= 0)
-                            reinterpret_cast<vec *>(ke + int64_t(k) * 8 * BS + (i0 + c) * kRow)[p - sl * kP] = x;
-                    }
-                    wave_lds_handoff();  // before the next row is staged
+                    for (int w = 0; w < W; ++w) x[w] = TV(o[v * W + w]);
+                    reinterpret_cast<vec *>(stage + lane * 4 * ND)[v] = x;
                 }
+                wave_lds_handoff();
+                constexpr int kP = kRow / W;  // pieces per row
+#pragma unroll
+                for (int t = 0; t < 32 * kP / 64; ++t) {
+                    const int p = lane + 64 * t, sl = p / kP;
+                    const int32_t k = slot(4 * round + sl / 8, sl % 8);
+                    const vec x = reinterpret_cast<const vec *>(stage)[p];
+                    if (k >= 0)
+                        reinterpret_cast<vec *>(ke + int64_t(k) * 8 * BS + i * kRow)[p - sl * kP] = x;
+                }
+                wave_lds_handoff();  // before the next row is staged
             }
         }
     }

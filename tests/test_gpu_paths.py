@@ -211,3 +211,26 @@ def test_j2_path_past_the_limit_load():
 
     out = bench.j2_path(fem, gen, 48, 96, fem.PRECOND_JACOBI, fem.PREC_FP64, 0, time_limit_s=60.0)
     assert abs(max(out["avg_sigma_zz"]) - 258.7) < 0.06 and abs(out["avg_sigma_zz"][-1] + 254.1) < 0.06
+
+
+# element counts with a remainder of the 8 elements of a wavefront; distorted and straight
+@pytest.mark.parametrize("law,shape", [("poisson", (9, 8, 7)), ("linear", (9, 8, 7)), ("linear", (13, 9, 5)),
+                                       ("nh", (9, 8, 7)), ("nh", (13, 9, 5)), ("simp", (24, 12, 6)), ("nh0", (10, 10, 10))])
+def test_fp32_tangent_is_symmetric_and_rounds_like_its_entries(law, shape):
+    """What Krylov methods react to beyond the largest entry's error.  The element entries
+    are formed in FP64, rounded once and summed in the same order on both sides of the
+    diagonal, so K = K^T up to entries that FP64 rounding pushes over an FP32 rounding
+    boundary: one in 10^4 off by 2^-23 would give 1e-9 of the norm.  Frobenius error: the
+    rounding of the element entries and of up to three sums per value, 2.4e-8 root mean
+    square each, 4.8e-8 together; one unit (2^-24) is allowed."""
+    p = {"simp": lambda: gen.simp_cantilever(*shape), "nh0": lambda: gen.nh_tensile(*shape, seed=2)}.get(
+        law, lambda: _line(law, *shape))()
+    u = np.zeros(p.n_dofs) if law == "nh0" else 0.002 * np.random.default_rng(5).standard_normal(p.n_dofs)
+    prob = fem.Problem(p, DEV)
+    _, K = prob.assemble(u, residual=False)
+    _, K32 = prob.assemble(u, residual=False, values_dtype=torch.float32)
+    K32 = K32.double()
+    perm = prob.export_pattern(slot_map=False)["transpose_perm"].long()
+    assert float((K32 - K32[perm]).norm() / K32.norm()) <= 1e-9
+    assert float((K32 - K).norm() / K.norm()) <= 2.0 ** -24
+    prob.close()
