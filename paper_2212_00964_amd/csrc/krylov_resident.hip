@@ -193,8 +193,20 @@ struct ResidentArgs {
     long long limit;   // clock ticks a workgroup waits for the others
 };
 
-// The rows of workgroup b: nodes [b chunk, (b + 1) chunk).  Eight lanes take one node, lane l
-// its neighbour blocks l, l + 8, l + 16, l + 24.  The first KN passes over the workgroup's
+// Neighbour block j of lane l8 of a node's eight, and the sum over the eight: with the lane's
+// blocks added in pairs (0, 1) and (2, 3), a row is summed in the order of the separate
+// kernels' 32 lanes (group32_sum) and rounds the same.
+__device__ __forceinline__ int lane_block(int l8, int j) { return 16 * (j & 1) + (j < 2 ? l8 : 15 - l8); }
+template <typename T>
+__device__ __forceinline__ T row_sum8(T v) {
+    v += dpp_read<kDppHalfMirror>(v);
+    v += dpp_read<kDppXor2>(v);
+    v += dpp_read<kDppXor1>(v);
+    return v;
+}
+
+// The rows of workgroup b: nodes [b chunk, (b + 1) chunk).  Eight lanes take one node, four of its
+// neighbour blocks each (lane_block).  The first KN passes over the workgroup's
 // nodes have their values in registers; of the others (MORE) as many as fit stay in LDS
 // and the rest are read from memory in every product.  Touched nodes are numbered for LDS: the workgroup's own first, then the
 // others in ascending order (found once by a bit map over all nodes; `hid` lists the
@@ -253,7 +265,7 @@ struct ResidentRows {
             const int s0 = ln < cnt ? rowp[ln] : 0, deg = ln < cnt ? rowp[ln + 1] - s0 : 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int l = l8 + 8 * j;
+                const int l = lane_block(l8, j);
                 nbm[k][j] = l < deg ? nb[b0 + s0 + l] : -1;
                 if (l < deg) mark(nbm[k][j]);
                 const TV *vb = values + int64_t(ND) * ND * (b0 + s0) + ND * l;
@@ -335,24 +347,34 @@ struct ResidentRows {
         const int l8 = threadIdx.x & 7, g8 = threadIdx.x / 8;
         auto finish = [&](int ln, T (&acc)[ND]) {
 #pragma unroll
-            for (int i = 0; i < ND; ++i) acc[i] = lane_sum8(acc[i]);
+            for (int i = 0; i < ND; ++i) acc[i] = row_sum8(acc[i]);
             T q = acc[0];
             if constexpr (ND == 3) q = l8 == 1 ? acc[1] : (l8 == 2 ? acc[2] : acc[0]);
             if (ln < cnt && l8 < ND) out(ln, q);
         };
-        auto add = [&](T (&acc)[ND], const TV (&w)[ND][ND], int at) {
+        // The products of a block.  (One chain of all 12 products of a lane left FP32 rows 8%
+        // further off than the separate kernels', 25% with one dof per node at 42^3.)
+        auto block = [&](T (&s)[ND], const TV (&w)[ND][ND], int at) {
             T xm[ND];
 #pragma unroll
             for (int c = 0; c < ND; ++c) xm[c] = x[at + c];
 #pragma unroll
-            for (int i = 0; i < ND; ++i)
+            for (int i = 0; i < ND; ++i) {
+                s[i] = T(0);
 #pragma unroll
-                for (int c = 0; c < ND; ++c) acc[i] += T(w[i][c]) * xm[c];
+                for (int c = 0; c < ND; ++c) s[i] += T(w[i][c]) * xm[c];
+            }
         };
-        // Block l8 + 8 j of a node outside the registers (its blocks s0 .. s0 + deg) from `src`, the
+        // a += b, not contracted with the products behind b
+        auto add = [&](T (&a)[ND], const T (&b)[ND]) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int i = 0; i < ND; ++i) a[i] += b[i];
+        };
+        // The lane's block j of a node outside the registers (its blocks s0 .. s0 + deg) from `src`, the
         // values of the blocks from `from` on; zeros and the zero entry where there is none.
         auto load = [&](const TV *src, int from, int s0, int deg, int j, TV (&w)[ND][ND], int &at) {
-            const int l = l8 + 8 * j;
+            const int l = lane_block(l8, j);
             const bool in = l < deg;
             const TV *vb = src + int64_t(ND) * ND * (s0 - from) + ND * l;
             at = in ? int(npos[s0 + l - rest]) : Hn * ND;
@@ -360,6 +382,20 @@ struct ResidentRows {
             for (int i = 0; i < ND; ++i)
 #pragma unroll
                 for (int c = 0; c < ND; ++c) w[i][c] = in ? vb[i * ND * deg + c] : TV(0);
+        };
+        // FP64 blocks of three dofs one at a time: two in flight spill registers
+        constexpr bool kOne = ND * sizeof(TV) > 12;
+        // acc += blocks j and j + 1
+        auto pair = [&](T (&acc)[ND], const TV *src, int from, int s0, int deg, int j0) {
+#pragma unroll 1
+            for (int j = j0; j < j0 + 2; ++j) {
+                TV w[ND][ND];
+                T s[ND];
+                int at;
+                load(src, from, s0, deg, j, w, at);
+                block(s, w, at);
+                add(acc, s);
+            }
         };
         auto row = [&](int ln, int end, int &s0, int &deg) {
             s0 = ln < end ? rowp[ln] : rest;
@@ -373,16 +409,22 @@ struct ResidentRows {
 #pragma unroll
             for (int i = 0; i < ND; ++i) acc[i] = T(0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (sizeof(TV) < sizeof(T)) {
-                    // converted here each time: out of the loop the FP64 values would
-                    // take twice the registers
+            for (int j = 0; j < 4; j += 2) {
+                T s[2][ND];
 #pragma unroll
-                    for (int i = 0; i < ND; ++i)
+                for (int q = 0; q < 2; ++q) {
+                    if constexpr (sizeof(TV) < sizeof(T)) {
+                        // converted here each time: out of the loop the FP64 values would
+                        // take twice the registers
 #pragma unroll
-                        for (int c = 0; c < ND; ++c) asm volatile("" : "+v"(v[k][j][i][c]));
+                        for (int i = 0; i < ND; ++i)
+#pragma unroll
+                            for (int c = 0; c < ND; ++c) asm volatile("" : "+v"(v[k][j + q][i][c]));
+                    }
+                    block(s[q], v[k][j + q], int(q ? pos[k][j / 2] >> 16 : pos[k][j / 2] & 0xffffu));
                 }
-                add(acc, v[k][j], int(j % 2 ? pos[k][j / 2] >> 16 : pos[k][j / 2] & 0xffffu));
+                add(s[0], s[1]);
+                add(acc, s[0]);
             }
             finish(k * kResGroups + g8, acc);
         }
@@ -390,36 +432,57 @@ struct ResidentRows {
         if constexpr (MORE) {
 #pragma unroll 1
             for (int l0 = kFirst; l0 < s1; l0 += kResGroups) {
-                T acc[ND];
+                T acc[ND], acc2[ND];
 #pragma unroll
-                for (int i = 0; i < ND; ++i) acc[i] = T(0);
+                for (int i = 0; i < ND; ++i) acc[i] = acc2[i] = T(0);
                 int ls, ld;
                 row(l0 + g8, s1, ls, ld);
+                if constexpr (kOne) {
+                    pair(acc, lv, rest, ls, ld, 0);
+                    pair(acc2, lv, rest, ls, ld, 2);
+                    add(acc, acc2);
+                } else {
 #pragma unroll 1
-                for (int j = 0; j < 4; ++j) {
-                    TV wl[ND][ND];
-                    int al;
-                    load(lv, rest, ls, ld, j, wl, al);
-                    add(acc, wl, al);
+                    for (int j = 0; j < 4; j += 2) {
+                        T s[2][ND];
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            TV wl[ND][ND];
+                            int al;
+                            load(lv, rest, ls, ld, j + q, wl, al);
+                            block(s[q], wl, al);
+                            asm volatile("" ::: "memory");
+                        }
+                        add(s[0], s[1]);
+                        add(acc, s[0]);
+                    }
                 }
                 finish(l0 + g8 < s1 ? l0 + g8 : cnt, acc);
             }
-            constexpr int U = sizeof(TV) == 8 ? 1 : 2;  // blocks in flight per lane
 #pragma unroll 1
             for (int l0 = s1; l0 < cnt; l0 += kResGroups) {
-                T acc[ND];
+                T acc[ND], acc2[ND];
 #pragma unroll
-                for (int i = 0; i < ND; ++i) acc[i] = T(0);
+                for (int i = 0; i < ND; ++i) acc[i] = acc2[i] = T(0);
                 int s0, deg;
                 row(l0 + g8, cnt, s0, deg);
+                if constexpr (kOne) {
+                    pair(acc, mem, 0, s0, deg, 0);
+                    pair(acc2, mem, 0, s0, deg, 2);
+                    add(acc, acc2);
+                } else {
 #pragma unroll 1
-                for (int j = 0; j < 4; j += U) {
-                    TV w[U][ND][ND];
-                    int at[U];
-#pragma unroll
-                    for (int q = 0; q < U; ++q) load(mem, 0, s0, deg, j + q, w[q], at[q]);
-#pragma unroll
-                    for (int q = 0; q < U; ++q) add(acc, w[q], at[q]);
+                    for (int j = 0; j < 4; j += 2) {
+                        T s[2][ND];
+                        TV w[2][ND][ND];
+                        int at[2];
+                        load(mem, 0, s0, deg, j, w[0], at[0]);
+                        load(mem, 0, s0, deg, j + 1, w[1], at[1]);
+                        block(s[0], w[0], at[0]);
+                        block(s[1], w[1], at[1]);
+                        add(s[0], s[1]);
+                        add(acc, s[0]);
+                    }
                 }
                 finish(l0 + g8, acc);
             }
