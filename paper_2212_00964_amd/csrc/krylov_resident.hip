@@ -732,7 +732,10 @@ __global__ __launch_bounds__(kResThreads, 2) void k_bicg_resident(ResidentArgs<T
             x[k] = e < nd ? a.x[d0 + e] : T(0);
             if (e < nd) hs[e] = a.rh[d0 + e];
         }
-        __syncthreads();
+        // all have read v before anyone's first product writes it
+        const double none[1] = {0.0};
+        double all[1];
+        if (!grid_sum<1>(a.slots, epoch++, a.limit, none, all)) return gave_up();
     }
     for (int it = a.it0; it < a.it_end && !converged && !breakdown; ++it) {
         {
@@ -937,7 +940,7 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
             h->res_epoch = 0;
         }
         a.epoch = h->res_epoch + 1;
-        h->res_epoch += 3 * kResItsPerLaunch + 8;
+        h->res_epoch += 3 * kResItsPerLaunch + 8;  // (at most two rounds before the first iteration)
         h->host_kry->aborted = 0;
         constexpr int kMax = resident_max<ND, TV>();
         if (pl.chunk > kMax * kResGroups) resident_launch<ND, resident_max_more<ND, TV>(), true, T, TV, CG>(pl, a, s);

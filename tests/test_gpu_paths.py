@@ -279,3 +279,24 @@ def test_one_kernel_products_round_like_the_separate_kernels(law, shape):
     one, sep = (_one_step_residuals(prob, loads, prof) for prof in (0, 1))
     assert one <= 1.04 * sep, (one, sep)
     prob.close()
+
+
+@pytest.mark.parametrize("shape", [(30, 26, 24), (42, 41, 40)])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_one_kernel_bicgstab_over_several_launches(shape, precision):
+    """2,064 iterations are three launches, each of which takes up the vectors of the one before: the
+    same bits every time.  With FP64 vectors the recursive residual is the true one up to
+    rounding, which 2,064 products leave at 1e-16 of iterates up to 1e3 |b| each: 1e-9 allowed."""
+    prob = fem.Problem(gen.cantilever(*shape, distort_seed=3), DEV)
+    seen = set()
+    for _ in range(6):
+        try:
+            _, st = prob.newton_solve(krylov=fem.BICGSTAB, precision=precision, krylov_max_it=2064, krylov_rtol=1e-30,
+                                      newton_fixed_its=1)
+        except fem.FemError as e:  # (FP32 vectors need not have reduced the residual here)
+            st = e.stats
+        seen.add((st.krylov_its_total, st.krylov_relres[0]))
+        if precision == 0:
+            assert abs(st.final_residual / st.initial_residual - st.krylov_relres[0]) <= 1e-9
+    assert len(seen) == 1, seen
+    prob.close()
