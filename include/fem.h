@@ -319,6 +319,19 @@ int fem_adjoint_vjp(fem_handle *h, const double *u, const double *theta, const d
                     double *lambda_out, const fem_solve_opts *opts, fem_solve_stats *stats, void *workspace,
                     size_t workspace_bytes, void *stream);
 
+/* Krylov solves of the handle that ran as one kernel, since it was built.  Solves on up to
+ * 1,024 dofs per compute unit (CG, and BiCGSTAB with point Jacobi; nodes with at most 32
+ * neighbours; not with profile_spmv) take that path; the others, and those that the
+ * last two counts name, run as separate kernels, with sums in another order. */
+typedef struct {
+    int64_t solves;   /* finished in one kernel */
+    int64_t launches; /* of that kernel, unfinished ones included (1,024 iterations each) */
+    int64_t misfits;  /* given back: the nodes a workgroup touches do not fit its LDS (found at the
+                         first solve of a method and precision, the next ones go past) */
+    int64_t gave_up;  /* given back: the workgroups were not all running within the time limit */
+} fem_one_kernel_counts;
+int fem_one_kernel_stats(fem_handle *h, fem_one_kernel_counts *counts);
+
 /* ------------------------------------------------------------------------------
  * Path-dependent state of FEM_J2_PLASTIC.  The history holds, for every element e and
  * Gauss point q, 12 FP64 values at [(e*8 + q)*12]: the total strain of the last

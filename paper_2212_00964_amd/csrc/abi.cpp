@@ -401,6 +401,13 @@ int fem_history_copy(fem_handle *h, double *buf, int32_t into_handle, void *stre
     });
 }
 
+int fem_one_kernel_stats(fem_handle *h, fem_one_kernel_counts *counts) {
+    return guarded([&] {
+        require(h != nullptr && counts != nullptr, "handle and counts must be non-NULL");
+        *counts = h->res_counts;
+    });
+}
+
 int fem_average_stress(fem_handle *h, double *out, void *stream) {
     return guarded([&] {
         require(h != nullptr && out != nullptr, "handle and out must be non-NULL");

@@ -167,6 +167,7 @@ struct fem_handle {
     unsigned res_epoch = 0;                   // last round number they used
     bool res_off = false;                     // their workgroups could not run together
     bool res_misfit[2][2][2] = {};            // [CG][FP64 vectors][FP64 values]: too many touched nodes
+    fem_one_kernel_counts res_counts = {};
     std::vector<void *> allocations;          // device allocations owned by the handle
     fem::Filter filter;                       // fem_filter_setup (owns its allocations)
     double *red_partials = nullptr;           // [kRedGrid] reduction partials (fem_element_volumes, fem_set_load)

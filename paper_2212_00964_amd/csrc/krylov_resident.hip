@@ -947,19 +947,25 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
         else if (pl.kn == 1) resident_launch<ND, 1, false, T, TV, CG>(pl, a, s);
         else if (pl.kn == 2) resident_launch<ND, 2, false, T, TV, CG>(pl, a, s);
         else resident_launch<ND, kMax, false, T, TV, CG>(pl, a, s);
+        h->res_counts.launches++;
         FEM_HIP(hipStreamSynchronize(s));
         hs = *h->host_kry;
         if (hs.aborted == kGaveUp) {
             // the workgroups were not all running together (compute units held by other
             // work): this solve and the handle's later ones take the separate kernels
             h->res_off = true;
+            h->res_counts.gave_up++;
             return false;
         }
         if (hs.aborted == kMisfit) {  // too many touched nodes for the LDS
             misfit = true;
+            h->res_counts.misfits++;
             return false;
         }
-        if (hs.converged || hs.breakdown || hs.its >= max_its) return true;
+        if (hs.converged || hs.breakdown || hs.its >= max_its) {
+            h->res_counts.solves++;
+            return true;
+        }
         a.it0 = hs.its;
     }
 }

@@ -82,6 +82,11 @@ class SolveStats(ctypes.Structure):
         return d
 
 
+class OneKernelCounts(ctypes.Structure):
+    _fields_ = [("solves", ctypes.c_int64), ("launches", ctypes.c_int64), ("misfits", ctypes.c_int64),
+                ("gave_up", ctypes.c_int64)]
+
+
 class MmaOpts(ctypes.Structure):
     _fields_ = [("xmin", ctypes.c_double), ("xmax", ctypes.c_double), ("move", ctypes.c_double),
                 ("asy_init", ctypes.c_double), ("asy_decr", ctypes.c_double), ("asy_incr", ctypes.c_double),
@@ -92,7 +97,7 @@ class MmaOpts(ctypes.Structure):
 # Names, in the order the header declares them (checked by the CPU test-suite).
 EXPORTS = ["fem_last_error", "fem_default_opts", "fem_build_pattern", "fem_pattern_host", "fem_destroy", "fem_pattern_export",
            "fem_values_count", "fem_load_vector", "fem_workspace_bytes", "fem_assemble", "fem_residual_noalloc", "fem_check", "fem_spmv",
-           "fem_apply_tangent", "fem_newton_solve", "fem_adjoint_vjp", "fem_history_copy", "fem_average_stress",
+           "fem_apply_tangent", "fem_newton_solve", "fem_adjoint_vjp", "fem_one_kernel_stats", "fem_history_copy", "fem_average_stress",
            "fem_amg_setup", "fem_amg_sizes", "fem_amg_export", "fem_amg_apply", "fem_param_vjp", "fem_element_volumes",
            "fem_filter_setup", "fem_filter_apply", "fem_vector_workspace_bytes", "fem_dot", "fem_mma_default_opts",
            "fem_mma_update", "fem_mass_apply", "fem_set_load", "fem_axpby", "fem_obs_misfit"]
@@ -131,6 +136,7 @@ def lib():
         "fem_apply_tangent": (ctypes.c_int, [vp, vp, vp, vp, vp, vp, sz, vp]),
         "fem_newton_solve": (ctypes.c_int, [vp, vp, vp, vp, P(SolveOpts), P(SolveStats), vp, sz, vp]),
         "fem_adjoint_vjp": (ctypes.c_int, [vp, vp, vp, vp, vp, vp, P(SolveOpts), P(SolveStats), vp, sz, vp]),
+        "fem_one_kernel_stats": (ctypes.c_int, [vp, P(OneKernelCounts)]),
         "fem_history_copy": (ctypes.c_int, [vp, vp, i32, vp]),
         "fem_average_stress": (ctypes.c_int, [vp, P(dbl), vp]),
         "fem_amg_setup": (ctypes.c_int, [vp]),
@@ -424,6 +430,12 @@ class Problem:
         """Replaces the external load vector (fem_set_load)."""
         f = self._f64(f, self.n_dofs)
         _check(lib().fem_set_load(self.handle, _ptr(f), _stream()))
+
+    def one_kernel_stats(self) -> OneKernelCounts:
+        """Krylov solves of this handle that ran as one kernel, and those given back (fem_one_kernel_stats)."""
+        c = OneKernelCounts()
+        _check(lib().fem_one_kernel_stats(self.handle, ctypes.byref(c)))
+        return c
 
     def history(self) -> torch.Tensor:
         """The J2 history [n_elems, 8, 12] (strain then stress per Gauss point; fem_history_copy)."""

@@ -300,3 +300,79 @@ def test_one_kernel_bicgstab_over_several_launches(shape, precision):
             assert abs(st.final_residual / st.initial_residual - st.krylov_relres[0]) <= 1e-9
     assert len(seen) == 1, seen
     prob.close()
+
+
+def _loaded(law, *shape):
+    """The line of elements with a load (without one the Poisson line solves nothing)."""
+    p = _line(law, *shape)
+    if law == "poisson":
+        p.f_nodal = np.random.default_rng(3).standard_normal(p.n_dofs)
+    return p
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (15, 1, 1), (20, 1, 1), (17, 7, 7)])
+def test_one_kernel_solves_with_one_dof_per_node(shape):
+    """The edges of test_resident_cg with a load, against the oracle; tolerances as there."""
+    p = _loaded("poisson", *shape)
+    u_ref = orc.newton_solve(p, linear="direct", rtol=1e-13)
+    prob = fem.Problem(p, DEV)
+    n = 0
+    for krylov in (fem.CG, fem.BICGSTAB):
+        for precision, newton, inner, tol in ((fem.PREC_FP64, 1e-11, 1e-8, 1e-10), (fem.PREC_MIXED, 1e-10, 1e-5, 1e-6),
+                                              (fem.PREC_MIXED_V64, 1e-10, 1e-5, 1e-6)):
+            u, st = prob.newton_solve(krylov=krylov, precision=precision, krylov_rtol=inner, newton_rtol=newton)
+            assert_parity(host(u), u_ref, tol, f"{shape} {krylov} precision {precision}")
+            n += st.n_hist
+    assert prob.one_kernel_stats().solves == n > 0
+    prob.close()
+
+
+# Which solves run in one kernel: (krylov, precision) over shapes at the edges of the rule -- 1,024
+# dofs per compute unit (341 nodes of three dofs), random numbers whose touched nodes do or do
+# not fit the LDS, and what the rule leaves out.
+@pytest.mark.parametrize("law,shape,krylov,precision,opts,relabel,path", [
+    ("poisson", (1, 1, 1), 0, 0, {}, False, "one"), ("poisson", (44, 41, 40), 0, 0, {}, False, "one"),
+    ("linear", (16, 7, 7), 0, 0, {}, False, "one"), ("linear", (16, 7, 7), 0, 1, {}, False, "one"),
+    ("linear", (16, 7, 7), 0, 0, dict(precond=1), False, "one"), ("linear", (16, 7, 7), 1, 0, {}, False, "one"),
+    ("linear", (16, 7, 7), 1, 2, {}, False, "one"), ("nh", (16, 7, 7), 1, 1, {}, False, "one"),
+    ("linear", (40, 30, 27), 0, 0, {}, False, "one"), ("linear", (42, 41, 40), 1, 2, {}, False, "one"),
+    ("linear", (42, 41, 40), 1, 1, {}, False, "one"), ("linear", (30, 26, 24), 0, 0, {}, True, "one"),
+    ("poisson", (30, 26, 24), 0, 0, {}, True, "one"),
+    ("linear", (42, 41, 40), 0, 0, {}, True, "misfit"), ("linear", (42, 41, 40), 1, 0, {}, True, "misfit"),
+    ("linear", (16, 7, 7), 1, 0, dict(precond=1), False, "separate"),
+    ("linear", (16, 7, 7), 0, 0, dict(profile_spmv=1), False, "separate"),
+    ("linear", (16, 7, 7), 0, 0, dict(precond=2), False, "separate"), ("fan", (19, 3, 0), 0, 0, {}, False, "separate")])
+def test_which_solves_run_in_one_kernel(law, shape, krylov, precision, opts, relabel, path):
+    p = gen.nh_fan(shape[0], shape[1]) if law == "fan" else _loaded(law, *shape)
+    if relabel:
+        p = gen.relabel(p, 7)[0]
+    prob = fem.Problem(p, DEV)
+    o = dict(krylov=krylov, precision=precision, krylov_rtol=1e-5, newton_rtol=1e-5, n_load_steps=1, **opts)
+    for n in (1, 2):
+        _, st = prob.newton_solve(**o)
+        c = prob.one_kernel_stats()
+        assert c.gave_up == 0
+        if path == "one":
+            assert c.misfits == 0 and c.solves >= n * 1 and c.launches >= c.solves
+        else:
+            assert c.solves == 0 and c.misfits == c.launches == (1 if path == "misfit" else 0)
+    if path == "one":
+        assert c.solves == 2 * st.n_hist
+    prob.close()
+
+
+@pytest.mark.parametrize("krylov,precision", [(0, 0), (1, 2)])
+def test_largest_system_in_one_kernel(krylov, precision):
+    """1,024 dofs per compute unit are 341 nodes of three dofs: 87,296 nodes on 256 units.  A column
+    of 4 (n + 1) nodes just below and just above; one Krylov interval is enough to see the path."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    nodes = 341 * cus
+    for n, one in (((nodes - 4) // 4, True), (nodes // 4, False)):
+        prob = fem.Problem(gen.cantilever(n, 1, 1, L=(float(n), 1.0, 1.0), traction=(1.0, 0.0, 0.0)), DEV)
+        try:
+            prob.newton_solve(krylov=krylov, precision=precision, krylov_max_it=16, newton_fixed_its=1)
+        except fem.FemError:
+            pass  # (16 iterations need not reduce the residual)
+        c = prob.one_kernel_stats()
+        assert (c.launches, c.misfits, c.gave_up) == ((1, 0, 0) if one else (0, 0, 0)), (n, c.launches)
+        prob.close()
