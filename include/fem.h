@@ -328,9 +328,17 @@ typedef struct {
     int64_t launches; /* of that kernel, unfinished ones included (1,024 iterations each) */
     int64_t misfits;  /* given back: the nodes a workgroup touches do not fit its LDS (found at the
                          first solve of a method and precision, the next ones go past) */
-    int64_t gave_up;  /* given back: the workgroups were not all running within the time limit */
+    int64_t gave_up;  /* given back: the workgroups were not all running within the time limit (other
+                         work held compute units); the next solve goes past too, and after give-ups
+                         in a row the next 2, 4 ... 64 */
 } fem_one_kernel_counts;
 int fem_one_kernel_stats(fem_handle *h, fem_one_kernel_counts *counts);
+
+/* Limits of the handle's one-kernel solves: how long a workgroup waits for the others
+ * before the solve is given back (default 100,000 us; 0 gives up at the first word that is
+ * not there yet) and the iterations of a launch (default 1,024, the most).  FEM_EINVAL
+ * outside [0, 10 s] or [1, 1024]. */
+int fem_one_kernel_limits(fem_handle *h, int64_t wait_us, int32_t launch_its);
 
 /* ------------------------------------------------------------------------------
  * Path-dependent state of FEM_J2_PLASTIC.  The history holds, for every element e and

@@ -408,6 +408,16 @@ int fem_one_kernel_stats(fem_handle *h, fem_one_kernel_counts *counts) {
     });
 }
 
+int fem_one_kernel_limits(fem_handle *h, int64_t wait_us, int32_t launch_its) {
+    return guarded([&] {
+        require(h != nullptr, "handle is NULL");
+        require(wait_us >= 0 && wait_us <= 10000000, "wait_us must be in [0, 10000000]");
+        require(launch_its >= 1 && launch_its <= 1024, "launch_its must be in [1, 1024]");
+        h->res_wait_us = wait_us;
+        h->res_launch_its = launch_its;
+    });
+}
+
 int fem_average_stress(fem_handle *h, double *out, void *stream) {
     return guarded([&] {
         require(h != nullptr && out != nullptr, "handle and out must be non-NULL");

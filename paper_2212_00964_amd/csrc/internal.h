@@ -165,7 +165,10 @@ struct fem_handle {
     int clock_khz = 100000;                   // rate of the device's wall clock
     unsigned long long *res_slots = nullptr;  // exchange lines of the one-kernel solves (krylov_resident.hip)
     unsigned res_epoch = 0;                   // last round number they used
-    bool res_off = false;                     // their workgroups could not run together
+    int res_skip = 0;                         // solves to go to the separate kernels (after a give-up)
+    int res_backoff = 1;                      // and how many after the next one
+    int64_t res_wait_us = 100000;             // what a workgroup waits for the others
+    int res_launch_its = 1024;                // iterations of a launch, at most 1,024
     bool res_misfit[2][2][2] = {};            // [CG][FP64 vectors][FP64 values]: too many touched nodes
     fem_one_kernel_counts res_counts = {};
     std::vector<void *> allocations;          // device allocations owned by the handle

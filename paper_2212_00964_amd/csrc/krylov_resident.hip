@@ -41,6 +41,7 @@ constexpr int kResDofs = 2;                  // owned dofs per thread
 constexpr int kSlotWords = 8;                // a 64-byte line per workgroup (see grid_sum)
 constexpr int kAllToAll = 160;               // more workgroups than this sum through workgroup 0
 constexpr int kResItsPerLaunch = 1024;
+constexpr int kResMaxBackoff = 64;           // solves skipped after a give-up, at most
 enum : int { kGaveUp = 1, kMisfit = 2 };     // why a launch left the solve undone
 constexpr size_t kResStaticLds = 1024;       // the sums' arrays
 
@@ -884,7 +885,7 @@ ResidentPlan resident_plan(const fem_handle *h) {
     constexpr int kMax = resident_max<ND, TV>();
     const Graph &g = h->g;
     ResidentPlan p;
-    if (g.max_deg < 1 || g.max_deg > kResMaxDeg || h->res_off) return p;
+    if (g.max_deg < 1 || g.max_deg > kResMaxDeg) return p;
     int kn = 1;
     while (kn < kMax && g.Nn > int64_t(kn) * kResGroups * std::min(ND == 1 ? 40 : 80, h->num_cus)) kn *= 2;
     const int64_t per = int64_t(kn) * kResGroups;
@@ -924,6 +925,10 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
     if (misfit) return false;
     const ResidentPlan pl = resident_plan<ND, T, TV, CG>(h);
     if (pl.kn == 0) return false;
+    if (h->res_skip > 0) {
+        h->res_skip--;
+        return false;
+    }
     const Graph &g = h->g;
     ResidentArgs<T, TV> a{};
     a.Nn = g.Nn, a.node_ptr = g.node_ptr, a.node_nb = g.node_nb, a.values = values;
@@ -931,10 +936,10 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
     a.sc = k.sc, a.host = h->host_kry, a.slots = h->res_slots;
     a.chunk = pl.chunk, a.lds = pl.lds, a.check_fit = pl.check_fit, a.bj = k.bj;
     a.rtol = rtol;
-    a.limit = 100ll * h->clock_khz;  // 100 ms
+    a.limit = h->res_wait_us * h->clock_khz / 1000;
     ComputeUnits share(h->device, pl.grid, h->num_cus);
     for (;;) {
-        a.it_end = int(std::min<int64_t>(max_its, int64_t(a.it0) + kResItsPerLaunch));
+        a.it_end = int(std::min<int64_t>(max_its, int64_t(a.it0) + h->res_launch_its));
         if (h->res_epoch > 0x70000000u) {  // round numbers of the far past must not come up again
             FEM_HIP(hipMemsetAsync(h->res_slots, 0, resident_slots_bytes(h), s));
             h->res_epoch = 0;
@@ -952,8 +957,10 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
         hs = *h->host_kry;
         if (hs.aborted == kGaveUp) {
             // the workgroups were not all running together (compute units held by other
-            // work): this solve and the handle's later ones take the separate kernels
-            h->res_off = true;
+            // work): the separate kernels take this solve and the next one, then, while it
+            // goes on, the next 2, 4 ... 64, so that waiting in vain stays a small part
+            h->res_skip = h->res_backoff;
+            h->res_backoff = std::min(2 * h->res_backoff, kResMaxBackoff);
             h->res_counts.gave_up++;
             return false;
         }
@@ -964,6 +971,7 @@ bool resident_solve(fem_handle *h, const KrylovVecs<T> &k, const TV *values, con
         }
         if (hs.converged || hs.breakdown || hs.its >= max_its) {
             h->res_counts.solves++;
+            h->res_backoff = 1;
             return true;
         }
         a.it0 = hs.its;

@@ -97,7 +97,7 @@ class MmaOpts(ctypes.Structure):
 # Names, in the order the header declares them (checked by the CPU test-suite).
 EXPORTS = ["fem_last_error", "fem_default_opts", "fem_build_pattern", "fem_pattern_host", "fem_destroy", "fem_pattern_export",
            "fem_values_count", "fem_load_vector", "fem_workspace_bytes", "fem_assemble", "fem_residual_noalloc", "fem_check", "fem_spmv",
-           "fem_apply_tangent", "fem_newton_solve", "fem_adjoint_vjp", "fem_one_kernel_stats", "fem_history_copy", "fem_average_stress",
+           "fem_apply_tangent", "fem_newton_solve", "fem_adjoint_vjp", "fem_one_kernel_stats", "fem_one_kernel_limits", "fem_history_copy", "fem_average_stress",
            "fem_amg_setup", "fem_amg_sizes", "fem_amg_export", "fem_amg_apply", "fem_param_vjp", "fem_element_volumes",
            "fem_filter_setup", "fem_filter_apply", "fem_vector_workspace_bytes", "fem_dot", "fem_mma_default_opts",
            "fem_mma_update", "fem_mass_apply", "fem_set_load", "fem_axpby", "fem_obs_misfit"]
@@ -137,6 +137,7 @@ def lib():
         "fem_newton_solve": (ctypes.c_int, [vp, vp, vp, vp, P(SolveOpts), P(SolveStats), vp, sz, vp]),
         "fem_adjoint_vjp": (ctypes.c_int, [vp, vp, vp, vp, vp, vp, P(SolveOpts), P(SolveStats), vp, sz, vp]),
         "fem_one_kernel_stats": (ctypes.c_int, [vp, P(OneKernelCounts)]),
+        "fem_one_kernel_limits": (ctypes.c_int, [vp, i64, i32]),
         "fem_history_copy": (ctypes.c_int, [vp, vp, i32, vp]),
         "fem_average_stress": (ctypes.c_int, [vp, P(dbl), vp]),
         "fem_amg_setup": (ctypes.c_int, [vp]),
@@ -436,6 +437,10 @@ class Problem:
         c = OneKernelCounts()
         _check(lib().fem_one_kernel_stats(self.handle, ctypes.byref(c)))
         return c
+
+    def one_kernel_limits(self, wait_us: int = 100000, launch_its: int = 1024):
+        """Wait and iteration limits of one-kernel launches (fem_one_kernel_limits)."""
+        _check(lib().fem_one_kernel_limits(self.handle, wait_us, launch_its))
 
     def history(self) -> torch.Tensor:
         """The J2 history [n_elems, 8, 12] (strain then stress per Gauss point; fem_history_copy)."""

@@ -376,3 +376,55 @@ def test_largest_system_in_one_kernel(krylov, precision):
         c = prob.one_kernel_stats()
         assert (c.launches, c.misfits, c.gave_up) == ((1, 0, 0) if one else (0, 0, 0)), (n, c.launches)
         prob.close()
+
+
+@pytest.mark.parametrize("krylov,precision", [(0, 0), (0, 1), (1, 0), (1, 2)])
+def test_one_kernel_solve_that_gives_up(krylov, precision):
+    """A wait limit of 0: the workgroups leave, the separate kernels solve from the start (the same
+    bits as when they are asked for), and the one kernel is tried again after 1, 2, 4 ... solves."""
+    prob = fem.Problem(gen.cantilever(30, 26, 24, distort_seed=3), DEV)
+    # one correction per call: what the wait costs is seen solve by solve
+    o = dict(krylov=krylov, precision=precision, krylov_rtol=1e-4, newton_fixed_its=1)
+    u_one, _ = prob.newton_solve(**o)
+    u_sep, _ = prob.newton_solve(profile_spmv=1, **o)
+    assert prob.one_kernel_stats().solves == 1
+    prob.one_kernel_limits(wait_us=0)
+    gave_up = []
+    for _ in range(8):
+        u, st = prob.newton_solve(**o)
+        assert st.krylov_unconverged == 0 and torch.equal(u, u_sep)
+        gave_up.append(prob.one_kernel_stats().gave_up)
+    assert gave_up == [1, 1, 2, 2, 2, 3, 3, 3]
+    prob.one_kernel_limits()
+    for _ in range(2):
+        prob.newton_solve(**o)  # (the last two of the four that go past)
+    for n in (2, 3):
+        u, _ = prob.newton_solve(**o)
+        assert torch.equal(u, u_one) and prob.one_kernel_stats().solves == n
+    c = prob.one_kernel_stats()
+    assert (c.gave_up, c.misfits, c.launches) == (3, 0, 6)
+    prob.close()
+
+
+@pytest.mark.parametrize("krylov,precision", [(0, 0), (0, 1), (1, 0), (1, 1), (1, 2)])
+@pytest.mark.parametrize("its", [1, 7, 100])
+def test_one_kernel_launches_continue_each_other(krylov, precision, its):
+    """The same solve in launches of 1, 7 and 100 iterations as in one of 1,024: the same bits."""
+    prob = fem.Problem(gen.cantilever(12, 11, 10, distort_seed=3), DEV)
+    o = dict(krylov=krylov, precision=precision, krylov_rtol=1e-4, newton_fixed_its=1)
+    u_one, st = prob.newton_solve(**o)
+    assert prob.one_kernel_stats().launches == 1
+    prob.one_kernel_limits(launch_its=its)
+    u, st2 = prob.newton_solve(**o)
+    n = st.krylov_its_total
+    assert torch.equal(u, u_one) and st2.krylov_its_total == n
+    assert prob.one_kernel_stats().launches == 1 + (n + its - 1) // its
+    prob.close()
+
+
+def test_one_kernel_limits_are_checked():
+    prob = fem.Problem(gen.cantilever(2, 2, 2), DEV)
+    for wait, its in ((-1, 1024), (10**7 + 1, 1024), (0, 0), (0, 1025)):
+        with pytest.raises(fem.FemError):
+            prob.one_kernel_limits(wait_us=wait, launch_its=its)
+    prob.close()
