@@ -830,10 +830,13 @@ __global__ __launch_bounds__(kResThreads, 2) void k_bicg_resident(ResidentArgs<T
 
 // Workgroups of resident solves on one device wait for one another, so all of them have to
 // fit the device at once: a solve takes its share of the compute units here before the
-// launch and gives it back when its kernel has ended (other threads' solves wait).
+// launch and gives it back when its kernel has ended (other threads' solves wait).  Workgroups
+// go to the 8 XCDs in turn, so what has to fit is what falls on the first one: with 250 + 6
+// workgroups on 256 compute units two XCDs would get 33 for their 32, and each kernel could
+// wait for the unit that the other holds.
 class ComputeUnits {
 public:
-    ComputeUnits(int device, int n, int total) : pool_(pool(device)), n_(n) {
+    ComputeUnits(int device, int n, int total) : pool_(pool(device)), n_(std::min((n + 7) / 8 * 8, total)) {
         std::unique_lock<std::mutex> lk(pool_.m);
         pool_.cv.wait(lk, [&] { return pool_.used + n_ <= total; });
         pool_.used += n_;

@@ -428,3 +428,36 @@ def test_one_kernel_limits_are_checked():
         with pytest.raises(fem.FemError):
             prob.one_kernel_limits(wait_us=wait, launch_its=its)
     prob.close()
+
+
+@pytest.mark.parametrize("shapes", [((30, 26, 24), (30, 26, 24)), ((19, 39, 39), (7, 7, 5)), ((40, 30, 27), (5, 4, 3))])
+def test_one_kernel_solves_share_the_device(shapes):
+    """Threads whose solves together need more workgroups than there are compute units (164 and 164),
+    as many, but too many of an XCD's (250 and 6), and nearly all (255 and 2): each takes its turn,
+    none gives up, and all results are those of a solve alone."""
+    import threading
+
+    probs = [fem.Problem(gen.cantilever(*s, E=70e3 * (1 + i)), DEV) for i, s in enumerate(shapes)]
+    opts = dict(krylov=fem.CG, krylov_rtol=1e-6, newton_rtol=1e-5)
+    alone = [q.newton_solve(**opts)[0].clone() for q in probs]
+    torch.cuda.synchronize()
+    same = [0, 0]
+
+    def work(i):
+        torch.cuda.set_device(0)
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(12):
+                u, _ = probs[i].newton_solve(**opts)
+                same[i] += int(torch.equal(u, alone[i]))
+
+    ths = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for th in ths:
+        th.start()
+    for th in ths:
+        th.join()
+    assert same == [12, 12]
+    for q in probs:
+        c = q.one_kernel_stats()
+        assert c.gave_up == 0 and c.solves == 13
+        q.close()
