@@ -237,7 +237,6 @@ void launch_export(const fem_handle *h, int64_t *row_ptr, int32_t *col_idx, int3
 
 // Fused Krylov kernels (grid-stride, FP64 reductions finished by the last block).
 int krylov_grid(const fem_handle *h);
-size_t krylov_partials_bytes(const fem_handle *h);
 
 template <typename T>
 struct KrylovVecs {

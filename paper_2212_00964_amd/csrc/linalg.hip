@@ -1251,8 +1251,6 @@ static int spmv_grid(const fem_handle *h) {
     return (ND == 1 ? 8 : (sizeof(TV) == 8 ? 2 : 3)) * h->num_cus;
 }
 
-size_t krylov_partials_bytes(const fem_handle *h) { return size_t(krylov_grid(h)) * 3 * sizeof(double); }
-
 template <int ND, typename T>
 static void spmv_launch(const fem_handle *h, const T *values, int transpose, const T *x, T *y, T alpha, T beta,
                         hipStream_t s) {
