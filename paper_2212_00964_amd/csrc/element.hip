@@ -462,65 +462,65 @@ __global__ __launch_bounds__(kThreads) void k_element_vec(int64_t Ne, const doub
             for (int i = 0; i < ND; ++i) out[int64_t(kpos[id.e * 8 + id.a]) * ND + i] = acc[i];
         }
     } else {
-    ElemIds id = elem_ids(Ne);
-    // corner of this lane: bits of c.  A step along direction 0 is lane ^ 1, along direction
-    // 1 lane ^ 2 and along direction 2 lane ^ 7 (each one DPP move).
-    const int c = id.a ^ ((id.a & 4) ? 3 : 0);
-    id.a = c ^ ((c >> 1) & 1);  // local node there
-    double X[3], U[ND], W[ND];
-    load_node<ND, LOAD_FIELD | LOAD_REL>(coords, conn, u, nullptr, id, X, U);
-    if (MODE != VEC_RESIDUAL)
-        load_node<ND, LOAD_FIELD | (MODE == VEC_LIFT ? 0 : LOAD_MASKED) | (MODE != VEC_VJP ? LOAD_REL : 0)>(
-                coords, conn, v, mask, id, X, W);
-    const double th = theta[id.e];
-    const double mod = (MODE == VEC_VJP) ? 1.0 : modulus(mat, th);
-    // J and the gradients come without the factor p^2 / 2 of every column and the sign s_k of
-    // column k: they cancel in G = Gr J^{-1} and, up to the signs of the sums' differences, in
-    // d P J^{-T} dN; only the determinant needs them.
-    double J[3][3], Gr[3][3] = {}, Wr[3][3] = {};
+        ElemIds id = elem_ids(Ne);
+        // corner of this lane: bits of c.  A step along direction 0 is lane ^ 1, along direction
+        // 1 lane ^ 2 and along direction 2 lane ^ 7 (each one DPP move).
+        const int c = id.a ^ ((id.a & 4) ? 3 : 0);
+        id.a = c ^ ((c >> 1) & 1);  // local node there
+        double X[3], U[ND], W[ND];
+        load_node<ND, LOAD_FIELD | LOAD_REL>(coords, conn, u, nullptr, id, X, U);
+        if (MODE != VEC_RESIDUAL)
+            load_node<ND, LOAD_FIELD | (MODE == VEC_LIFT ? 0 : LOAD_MASKED) | (MODE != VEC_VJP ? LOAD_REL : 0)>(
+                    coords, conn, v, mask, id, X, W);
+        const double th = theta[id.e];
+        const double mod = (MODE == VEC_VJP) ? 1.0 : modulus(mat, th);
+        // J and the gradients come without the factor p^2 / 2 of every column and the sign s_k of
+        // column k: they cancel in G = Gr J^{-1} and, up to the signs of the sums' differences, in
+        // d P J^{-T} dN; only the determinant needs them.
+        double J[3][3], Gr[3][3] = {}, Wr[3][3] = {};
 #pragma unroll
-    for (int i = 0; i < 3; ++i) corner_grad(X[i], J[i]);
+        for (int i = 0; i < 3; ++i) corner_grad(X[i], J[i]);
 #pragma unroll
-    for (int i = 0; i < ND; ++i) corner_grad(U[i], Gr[i]);
-    if constexpr (kDir)
+        for (int i = 0; i < ND; ++i) corner_grad(U[i], Gr[i]);
+        if constexpr (kDir)
 #pragma unroll
-        for (int i = 0; i < ND; ++i) corner_grad(W[i], Wr[i]);
-    const double dj = det3(J);
-    const double d = (__popc(c) & 1) ? kCornerDet * dj : -kCornerDet * dj;
-    const bool mesh_ok = d > 0.0;
-    double Bt[3][3];
-    inv_transpose3(J, dj, Bt);
-    double G[3][3], dG[3][3], P[3][3];
+            for (int i = 0; i < ND; ++i) corner_grad(W[i], Wr[i]);
+        const double dj = det3(J);
+        const double d = (__popc(c) & 1) ? kCornerDet * dj : -kCornerDet * dj;
+        const bool mesh_ok = d > 0.0;
+        double Bt[3][3];
+        inv_transpose3(J, dj, Bt);
+        double G[3][3], dG[3][3], P[3][3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            G[i][j] = Gr[i][0] * Bt[j][0] + Gr[i][1] * Bt[j][1] + Gr[i][2] * Bt[j][2];
-            dG[i][j] = Wr[i][0] * Bt[j][0] + Wr[i][1] * Bt[j][1] + Wr[i][2] * Bt[j][2];
+            for (int j = 0; j < 3; ++j) {
+                G[i][j] = Gr[i][0] * Bt[j][0] + Gr[i][1] * Bt[j][1] + Gr[i][2] * Bt[j][2];
+                dG[i][j] = Wr[i][0] * Bt[j][0] + Wr[i][1] * Bt[j][1] + Wr[i][2] * Bt[j][2];
+            }
+        bool mat_ok;
+        if constexpr (kDir) mat_ok = dflux_mat<MODEL, double>(mat, mod, G, dG, P, nullptr);
+        else mat_ok = flux_mat<MODEL, double>(mat, mod, G, P, nullptr);
+        double acc[ND];
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            double M[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) M[k] = d * (P[i][0] * Bt[0][k] + P[i][1] * Bt[1][k] + P[i][2] * Bt[2][k]);
+            acc[i] = corner_div(M);
         }
-    bool mat_ok;
-    if constexpr (kDir) mat_ok = dflux_mat<MODEL, double>(mat, mod, G, dG, P, nullptr);
-    else mat_ok = flux_mat<MODEL, double>(mat, mod, G, P, nullptr);
-    double acc[ND];
+        if (id.valid && (!mesh_ok || !mat_ok))
+            atomicOr(status, (!mesh_ok ? ST_MESH : 0) | (!mat_ok ? ST_INVERTED : 0));
+        if (MODE == VEC_VJP) {
+            double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < ND; ++i) {
-        double M[3];
+            for (int i = 0; i < ND; ++i) s += W[i] * acc[i];
+            s = sum8(s);
+            if (id.valid && id.a == 0) out[id.e] = -dmodulus(mat, th) * s;
+        } else if (id.valid) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) M[k] = d * (P[i][0] * Bt[0][k] + P[i][1] * Bt[1][k] + P[i][2] * Bt[2][k]);
-        acc[i] = corner_div(M);
-    }
-    if (id.valid && (!mesh_ok || !mat_ok))
-        atomicOr(status, (!mesh_ok ? ST_MESH : 0) | (!mat_ok ? ST_INVERTED : 0));
-    if (MODE == VEC_VJP) {
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < ND; ++i) s += W[i] * acc[i];
-        s = sum8(s);
-        if (id.valid && id.a == 0) out[id.e] = -dmodulus(mat, th) * s;
-    } else if (id.valid) {
-#pragma unroll
-        for (int i = 0; i < ND; ++i) out[int64_t(kpos[id.e * 8 + id.a]) * ND + i] = acc[i];
-    }
+            for (int i = 0; i < ND; ++i) out[int64_t(kpos[id.e * 8 + id.a]) * ND + i] = acc[i];
+        }
     }
 }
 
