@@ -959,9 +959,10 @@ __global__ __launch_bounds__(256) void k_extract_binv(int64_t Nn, const int64_t 
 // block.  |dK| / |K| and |K - K^T| / |K| of the FP32 tangent, factorised in FP32 / block by block
 // in FP32 (k_element_tangent) / now: 40^3 neo-Hookean 1.28e-7, 5.1e-8 / 9.3e-8, 6.2e-8 / 4.0e-8, 0;
 // 120x60x30 densities 9.7e-9, 1.4e-9 / 4.8e-9, 2.1e-9 / 2.1e-9, 0.
-// What bounds it: at 100^3 with FP32 values instruction issue (4,000 vector instructions per
-// wavefront, 0.8 ms, not all of it under the 2.4 GB it writes; FP32 sums took 0.24 ms less).
-// The 72 sums of all three rows at once spill (2.1 ms).  With FP64 values the 4.8 GB.
+// What bounds it: at 100^3 with FP32 values (975 us) instruction issue -- 2,860 vector
+// instructions per wavefront, two wavefronts per SIMD that issue 43% of the time each -- with the
+// 2.4 GB it writes beside it; FP32 sums took 832 us.  (The 72 sums of all three rows at once
+// spill: 2.1 ms.)  With FP64 values the 4.8 GB, 1,481 us.
 // Whole tangent, element kernel and gather, with k_element_tangent -> now, us: 100^3 FP32
 // 1,727 -> 1,773, FP64 3,776 -> 2,650 (linear 1,522 -> 1,507 and 3,570 -> 2,493, Poisson 492 -> 380
 // and 1,291 -> 503); 37x29x23 64 -> 58 and 126 -> 69; 10^3 28.6 -> 21.5 and 38.6 -> 20.3.

@@ -12,15 +12,15 @@
 // two blocks ahead in FP64, spills registers and costs 5 us more).
 // Time per iteration on box meshes, separate kernels -> this one, us (rows beyond the
 // registers from 32,768 nodes on with 8-byte values, 65,536 with 4-byte ones or one dof):
-//   CG, FP64        N = 675 11.5 -> 4.6, 12,675 11.5 -> 6.6, 91,875 18.9 -> 9.7,
-//                   212,355 32.1 -> 19.5, 260,925 37.1 -> 24.3
-//   CG, FP32        91,875 13.4 -> 8.6, 186,219 19.6 -> 10.1, 260,925 23.5 -> 15.9
-//   CG, FP32, one dof per node      9,261 14.6 -> 6.3, 64,000 17.1 -> 8.7, 250,047 30.3 -> 16.0
-//   BiCGSTAB, FP64  3,993 18.5 -> 10.2, 98,304 38.2 -> 18.3, 206,763 59.0 -> 44.9
-//   BiCGSTAB, FP32 values under FP64 vectors      46,875 23.1 -> 17.7, 192,000 41.0 -> 23.9,
-//                   206,763 43.3 -> 32.0, 255,552 47.9 -> 42.2
-//   BiCGSTAB, FP32  98,304 28.3 -> 16.7, 206,763 41.5 -> 26.2
-// With random node numbers a workgroup touches more nodes: CG, FP64, 91,875 25.1 -> 12.3;
+//   CG, FP64        N = 675 11.5 -> 5.4, 12,675 11.6 -> 6.3, 91,875 18.7 -> 9.4,
+//                   212,355 31.8 -> 19.5, 260,925 36.8 -> 24.5
+//   CG, FP32        91,875 13.5 -> 8.2, 186,219 20.0 -> 10.3, 260,925 23.4 -> 14.6
+//   CG, FP32, one dof per node      9,261 13.1 -> 5.5, 64,000 16.5 -> 8.3, 250,047 30.0 -> 14.7
+//   BiCGSTAB, FP64  3,993 17.4 -> 10.1, 98,304 37.7 -> 18.1, 206,763 59.2 -> 43.7
+//   BiCGSTAB, FP32 values under FP64 vectors      46,875 23.1 -> 18.3, 192,000 40.9 -> 24.4,
+//                   206,763 43.4 -> 30.4, 255,552 47.8 -> 38.0
+//   BiCGSTAB, FP32  98,304 28.4 -> 16.7, 206,763 41.7 -> 24.0
+// With random node numbers a workgroup touches more nodes: CG, FP64, 91,875 25.0 -> 12.3;
 // where they do not fit the LDS the separate kernels run (CG, FP64 from 186,219).
 #include <algorithm>
 #include <condition_variable>
@@ -77,7 +77,7 @@ __device__ __forceinline__ double uniform(double v) {
 // 9.4 through workgroup 0; with 148 workgroups 8.0 and 8.1, with 69 workgroups 6.8 and 7.8.
 // 32-byte slots cost the FP32 solve of the same mesh 0.7 us an iteration, slots packed
 // into shared lines 2 to 3 us; fences at agent scope (which write back and
-// invalidate L2) in place of the write-through accesses 13 us a round.
+// invalidate L2) in place of the write-through accesses 10 to 17 us a round.
 //
 // Vector data: what the workgroup stored with store_agent before the call (the wait below)
 // is what the others read with load_agent after it.  The wait for lines is bounded by the
@@ -882,7 +882,7 @@ constexpr int resident_max_more() { return ND == 1 ? 4 : (sizeof(TV) == 4 ? 3 : 
 // FP32 values under FP64 vectors, N = 14,739 17.1 / 12.1 / 12.3 us; 46,875 17.7 / 17.7 / 16.3;
 // CG, FP64, 4,131 6.5 / 6.0 / 6.0; 26,877 7.8 / 7.8 / 8.3; CG, FP32, 26,877 7.7 / 6.9 / 7.7; one
 // dof per node, 9,261 6.4 / 6.8 / 8.2 and 6.3 at 40.  At most two owned dofs per thread
-// (1,024 a workgroup: 87,381 nodes of three dofs on 256 CUs).
+// (1,024 a workgroup, so 341 nodes of three: 87,296 nodes on 256 CUs).
 template <int ND, typename T, typename TV, bool CG>
 ResidentPlan resident_plan(const fem_handle *h) {
     constexpr int kMax = resident_max<ND, TV>();

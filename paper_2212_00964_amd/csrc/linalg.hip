@@ -39,10 +39,13 @@ __device__ __forceinline__ T group_sum(T v) {
 
 // y = alpha K^T x + beta y.  A 32-lane group takes one node, lane = neighbour block: block
 // (n, m) of K^T is the transpose of block (m, n), whose place in node m's rows `mirror`
-// gives.  Four dependent loads per block (neighbour and mirror, row start of m, values and
-// x) with nothing to reuse, so what counts is how many are in flight: every lane handles
-// one block, eight wavefronts per SIMD, and the group's sums end in a reduce-scatter.
-// FP64, 41x33x27 (9.6 M entries): 22.9 us; with 16 lanes and two blocks each in a row 35.7 us.
+// gives.  Four dependent loads per block (row start of n, neighbour and mirror, row start of
+// m, values and x) with nothing to reuse, so what counts is how many are in flight: every
+// lane handles one block, eight wavefronts per SIMD, and the group's sums end in a
+// reduce-scatter.  41x33x27 (9.6 M entries), against 16 lanes with two blocks each in a row:
+// FP64 35.7 -> 22.9 us where the matrix is still in the Infinity Cache from the product before,
+// 10% less on one that is not (ten matrices in turn, 8 us of event timing included: FP64
+// 43.5 -> 39.0 us, FP32 37.5 -> 28.7).
 template <int ND, typename T>
 __global__ __launch_bounds__(kThreads, 8) void k_spmv_t(int64_t Nn, const int64_t *__restrict__ node_ptr,
                                                         const int32_t *__restrict__ node_nb,
@@ -264,12 +267,13 @@ struct GatherIn {
 // MODE 2: y = K x and omega = (w0, y) / (y, y), w0 = s      (BiCGSTAB t = K sh)
 //
 // What bounds it: bytes from HBM, or from the 256 MB Infinity Cache when the matrix
-// fits there.  The values are read with ordinary (cached) loads: a lane's 12- or 24-byte
-// pieces and the rows of neighbouring nodes share cache lines, which non-temporal loads
-// gave up before their second use, and they also kept small matrices out of the
-// Infinity Cache.  One node in flight per group and few resident blocks (spmv_grid):
-// the fewer streams an XCD runs, the more of the x gathers and split lines its 4 MB L2
-// serves.  Back-to-back products on box meshes, non-temporal loads with 4 / 4 / 2 nodes
+// fits there.  The values are read with ordinary (cached) loads: non-temporal ones kept small
+// matrices out of the Infinity Cache, and a lane's 12- or 24-byte pieces and the rows of
+// neighbouring nodes share cache lines.  One node in flight per group and few resident
+// blocks (spmv_grid).  The gain is not one of traffic: beyond L2 the 100^3 product moves 1.31
+// instead of 1.19 GB with FP32 values under FP64 vectors, 1.18 instead of 1.15 with FP32 vectors and
+// 2.25 instead of 2.28 in FP64, at a higher rate (4.50 -> 5.89 TB/s of algorithmic bytes in
+// FP64).  Back-to-back products on box meshes, non-temporal loads with 4 / 4 / 2 nodes
 // in flight on every resident block against this form:
 //   FP64, 100^3 (2.08 GB)     461.8 -> 352.2 us (4.50 -> 5.89 TB/s)
 //   FP64, 64x32x32 (138 MB)    36.8 ->  22.4 us (3.76 -> 6.17 TB/s)
